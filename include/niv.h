@@ -270,9 +270,9 @@ niv_status niv_query_half(niv_handle *h, const niv_half_frame *f, const niv_upsa
 /* Times the fused query on these frames for each candidate launch shape
  * (workgroup of 256 or 512 threads, and 768 for the lane-sliced 6-D field at
  * FP16/BF16, x 1, 2 or all-resident workgroups per CU x tile order: plain,
- * or XCD-grouped, where each of the 8 XCDs walks a contiguous eighth of the
- * tiles so that neighbouring pixels share an L2; best of 10 launches) and
- * keeps the fastest for later calls at this precision.  Synchronises
+ * or XCD-grouped, where the tiles go to the 8 XCDs in strips so that
+ * neighbouring pixels share an L2; best of 10 launches) and keeps the
+ * fastest for later calls at this precision.  Synchronises
  * `stream`; the frames' outputs are overwritten.  out (optional, host): the
  * n <= 24 candidates and their times, and the chosen shape. */
 typedef struct {

@@ -225,9 +225,12 @@ static void fill_args(const niv_handle *h, const niv_frame *frames, int n, niv_p
     }
 }
 
-static LaunchTune tune_of(const niv_handle *h, niv_precision prec)
+static LaunchTune tune_of(const niv_handle *h, niv_precision prec, const QueryArgs &a)
 {
-    return h->m.tuned[prec] ? h->m.tune[prec] : default_tune(h->m.kind, prec);
+    if (h->m.tuned[prec]) return h->m.tune[prec];
+    int64_t chunks = 0;
+    for (int f = 0; f < a.n_frames; ++f) chunks += (a.f[f].count + 63) / 64;
+    return default_tune(h->m.kind, prec, chunks);
 }
 
 niv_status niv_query(niv_handle *h, const niv_frame *frames, int32_t n_frames, niv_precision prec,
@@ -235,11 +238,11 @@ niv_status niv_query(niv_handle *h, const niv_frame *frames, int32_t n_frames, n
 {
     niv_status s = check_frames(h, frames, n_frames, prec);
     if (s != NIV_OK) return s;
-    const LaunchTune tu = tune_of(h, prec);
     for (int f0 = 0; f0 < n_frames; f0 += kMaxFrames) {
         const int n = n_frames - f0 < kMaxFrames ? n_frames - f0 : kMaxFrames;
         QueryArgs a;
         fill_args(h, frames + f0, n, prec, a);
+        const LaunchTune tu = tune_of(h, prec, a);
         a.xcd_order = tu.xcd_order;
         if (launch_query(h->m, a, prec, tu, stream) != hipSuccess) return NIV_ERR_HIP;
     }
@@ -252,9 +255,9 @@ niv_status niv_probe_encode(niv_handle *h, const niv_frame *frame, niv_precision
     niv_status s = check_frames(h, frame, 1, prec);
     if (s != NIV_OK) return s;
     if (h->m.kind != kRoom) return NIV_ERR_UNSUPPORTED;
-    const LaunchTune tu = tune_of(h, prec);
     QueryArgs a;
     fill_args(h, frame, 1, prec, a);
+    const LaunchTune tu = tune_of(h, prec, a);
     a.xcd_order = tu.xcd_order;
     return hip_status(launch_query_probe(h->m, a, prec, tu, stream));
 }
@@ -338,7 +341,7 @@ niv_status niv_query_half(niv_handle *h, const niv_half_frame *f, const niv_upsa
     fill_args(h, &q, 1, prec, a);
     a.f[0].sub_w = (f->width + 1) / 2;
     a.f[0].src_w = f->width;
-    const LaunchTune tu = tune_of(h, prec);
+    const LaunchTune tu = tune_of(h, prec, a);
     a.xcd_order = tu.xcd_order;
     if (launch_query(h->m, a, prec, tu, stream) != hipSuccess) return NIV_ERR_HIP;
     return hip_status(upsample_launch(h, f, p, stream));
@@ -378,7 +381,7 @@ static niv_status query_fallback_into(niv_handle *h, const niv_frame *frames, in
     a.fb_count = cnt;
     a.fb_cap = cap;
     a.fb_mask = fb->flag_mask;
-    const LaunchTune tu = tune_of(h, prec);
+    const LaunchTune tu = tune_of(h, prec, a);
     a.xcd_order = tu.xcd_order;
     if (launch_query(h->m, a, prec, tu, stream) != hipSuccess) return NIV_ERR_HIP;
     FbArgs b;
@@ -496,7 +499,7 @@ niv_status niv_autotune(niv_handle *h, const niv_frame *frames, int32_t n_frames
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess) return NIV_ERR_HIP;
     if (hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); return NIV_ERR_HIP; }
-    LaunchTune best = default_tune(h->m.kind, prec);
+    LaunchTune best = {512, 0, 0};   // replaced by the first candidate
     float best_ms = 1e30f;
     int k = 0;
     niv_status st = NIV_OK;

@@ -92,9 +92,10 @@ enum ModelKind { kUnitCube = 0, kRoom = 1, kWide6D = 2, kPE16 = 3, kPE32 = 4, kP
 struct LaunchTune {
     int block;
     int blocks_per_cu;
-    int xcd_order;   // 1: each XCD walks a contiguous eighth of the tiles
+    int xcd_order;   // 1: the tiles go to the XCDs in strips of kStrip
 };
-constexpr int kXcds = 8;  // workgroups are dealt to the XCDs round robin
+constexpr int kXcds = 8;     // workgroups are dealt to the XCDs round robin
+constexpr int kStrip = 32;   // tiles of a strip (16,384 pixels with 512 threads)
 
 // Operand-block layout of a prepared model (see the prepare kernel).
 struct OpLayout {
@@ -122,7 +123,8 @@ hipError_t launch_prepare(const Model &m, const float *params, void *prepared,
 // The weight operands of a prepared model only (trainable shapes, FP32/FP16).
 hipError_t launch_prepare_operands(const Model &m, const float *params, void *prepared,
                                    niv_precision prec, hipStream_t stream);
-LaunchTune default_tune(int kind, niv_precision prec);
+// chunks: 64-pixel chunks of the call
+LaunchTune default_tune(int kind, niv_precision prec, int64_t chunks);
 hipError_t launch_query(const Model &m, QueryArgs &a, niv_precision prec, const LaunchTune &tu,
                         hipStream_t stream);
 hipError_t launch_zero_u32(uint32_t *p, int n, hipStream_t stream);

@@ -168,9 +168,11 @@ template <int P, class S, bool WLDS, int BLOCK> constexpr size_t query_lds()
 constexpr size_t kLdsPerCu = 160 * 1024;
 
 template <int P, class S, bool WLDS, int TB, int BLOCK, bool PROBE = false>
-static hipError_t query_t(QueryArgs &a, int blocks_per_cu, hipStream_t st)
+static hipError_t query_t(QueryArgs &a, const LaunchTune &tu, hipStream_t st)
 {
-    constexpr int kWavesPerBlock = BLOCK / 64;
+    // a smaller workgroup than the instantiation's runs the same kernel
+    const int threads = (BLOCK == 256 && tu.block < BLOCK) ? tu.block : BLOCK;
+    const int waves = threads / 64;
     auto kern = k_query<P, S, WLDS, TB, false, BLOCK, PROBE>;
     constexpr size_t lds = query_lds<P, S, WLDS, BLOCK>();
     static_assert(lds <= kLdsPerCu, "workgroup LDS");
@@ -190,19 +192,19 @@ static hipError_t query_t(QueryArgs &a, int blocks_per_cu, hipStream_t st)
         if (e != hipSuccess) return e;
         max_blocks = nb > 0 ? nb : 1;
     }
-    // tiles: each block handles kWavesPerBlock chunks of 64 pixels of one frame
+    // tiles: each block handles one chunk of 64 pixels of one frame per wave
     int64_t t = 0;
     for (int f = 0; f < a.n_frames; ++f) {
         a.f[f].tile_begin = t;
         const int64_t chunks = (a.f[f].count + 63) / 64;
-        t += (chunks + kWavesPerBlock - 1) / kWavesPerBlock;
+        t += (chunks + waves - 1) / waves;
     }
     a.n_tiles = t;
     if (t == 0) return hipSuccess;
-    const int per_cu = (blocks_per_cu > 0 && blocks_per_cu < max_blocks) ? blocks_per_cu : max_blocks;
+    const int per_cu = (tu.blocks_per_cu > 0 && tu.blocks_per_cu < max_blocks) ? tu.blocks_per_cu : max_blocks;
     const int64_t cap = (int64_t)per_cu * n_cu;
     const int64_t blocks = t < cap ? t : cap;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(BLOCK), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3((unsigned)threads), lds, st, a);
     return hipGetLastError();
 }
 
@@ -212,14 +214,14 @@ static hipError_t query_b(QueryArgs &a, const LaunchTune &tu, hipStream_t st)
     // lane-sliced shapes keep no per-wave rows in LDS: a 768-thread
     // workgroup (three waves per SIMD) fits beside their weights
     if constexpr (S::SL) {
-        if (tu.block == 768) return query_t<P, S, WLDS, TB, 768>(a, tu.blocks_per_cu, st);
+        if (tu.block == 768) return query_t<P, S, WLDS, TB, 768>(a, tu, st);
     }
     // shapes whose 512-thread workgroup would not fit in LDS run 256 threads
     if constexpr (query_lds<P, S, WLDS, 512>() > kLdsPerCu) {
-        return query_t<P, S, WLDS, TB, 256>(a, tu.blocks_per_cu, st);
+        return query_t<P, S, WLDS, TB, 256>(a, tu, st);
     } else {
-        if (tu.block == 256) return query_t<P, S, WLDS, TB, 256>(a, tu.blocks_per_cu, st);
-        return query_t<P, S, WLDS, TB, 512>(a, tu.blocks_per_cu, st);
+        if (tu.block <= 256) return query_t<P, S, WLDS, TB, 256>(a, tu, st);
+        return query_t<P, S, WLDS, TB, 512>(a, tu, st);
     }
 }
 
@@ -228,10 +230,10 @@ template <int P>
 static hipError_t probe_b(QueryArgs &a, const LaunchTune &tu, hipStream_t st)
 {
     if constexpr (query_lds<P, ShapeRoom, true, 512>() > kLdsPerCu) {
-        return query_t<P, ShapeRoom, true, 4, 256, true>(a, tu.blocks_per_cu, st);
+        return query_t<P, ShapeRoom, true, 4, 256, true>(a, tu, st);
     } else {
-        if (tu.block == 256) return query_t<P, ShapeRoom, true, 4, 256, true>(a, tu.blocks_per_cu, st);
-        return query_t<P, ShapeRoom, true, 4, 512, true>(a, tu.blocks_per_cu, st);
+        if (tu.block <= 256) return query_t<P, ShapeRoom, true, 4, 256, true>(a, tu, st);
+        return query_t<P, ShapeRoom, true, 4, 512, true>(a, tu, st);
     }
 }
 
@@ -244,14 +246,34 @@ hipError_t launch_query_probe(const Model &m, QueryArgs &a, niv_precision prec, 
     return probe_b<NIV_BF16>(a, tu, st);
 }
 
-LaunchTune default_tune(int kind, niv_precision prec)
+// Launch shape where none was tuned.  Times in us, 256 / 512 threads (768:
+// the lane-sliced field), 1920x1080 room frames.
+LaunchTune default_tune(int kind, niv_precision prec, int64_t chunks)
 {
+    constexpr int64_t kCus = 256;
     LaunchTune t;
-    // FP32 operands need twice the LDS per wave; smaller workgroups fit more
-    // of them; the lane-sliced 6-D field runs three waves per SIMD
-    t.block = (prec == NIV_FP32 && kind != kWide6D) ? 256 : (kind == kWide6D && prec != NIV_FP32) ? 768 : 512;
     t.blocks_per_cu = 0;
-    t.xcd_order = 1;
+    // the grid-free networks read no grid: the order is indifferent
+    const bool pe = kind == kPE16 || kind == kPE32 || kind == kPE64;
+    t.xcd_order = pe ? 0 : 1;
+    t.block = 512;   // room FP16 176/168, BF16 248/238, FP32 628/515, g8 FP16 108/100
+    // the lane-sliced 6-D field runs three waves per SIMD (BF16 512: 2000, 768: 1875)
+    if (kind == kWide6D && prec != NIV_FP32) t.block = 768;
+    // FP16 PE16 46/54, PE32 53/58: short kernels whose LDS lets smaller workgroups fill the chip
+    if ((kind == kPE16 || kind == kPE32) && prec == NIV_FP16) t.block = 256;
+    // Calls that leave the chip idle: one chunk's gathers keep the texture
+    // path of a CU busy for ~8 us (points far apart), so the chunks are first
+    // spread over the CUs (4,133 points, room FP16: 8 waves per workgroup
+    // 57 us, one wave 22 us).
+    if (kind == kWide6D && prec != NIV_FP32) {
+        if (chunks <= 4 * kCus) t.block = 256;
+    } else if (chunks <= kCus) {
+        t.block = 64;
+    } else if (chunks <= 2 * kCus) {
+        t.block = 128;
+    } else if (chunks <= 4 * kCus) {
+        t.block = 256;
+    }
     return t;
 }
 

@@ -56,7 +56,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(query_min
 void k_query(const QueryArgs a)
 {
     static_assert(!PROBE || (!TRAIN && !S::SL), "probe: staged query encoding");
-    constexpr int kWavesPerBlock = BLOCK / 64;
+    // BLOCK threads at most; small calls launch 64 or 128
+    const int n_threads = BLOCK > 256 ? BLOCK : (int)blockDim.x, n_waves = n_threads / 64;
     using O = Ops<P, S>;
     static_assert(!TRAIN || (TB == 4 && P != NIV_BF16), "training: four tiles, FP32 or FP16");
     static_assert(!S::SL || WLDS, "lane slices read the level table from LDS");
@@ -76,17 +77,20 @@ void k_query(const QueryArgs a)
     uint32_t *stage = reinterpret_cast<uint32_t *>(smem + (WLDS ? O::W_BYTES : 0)) + wave * 64 * O::ROW_DW;
     int staged = -1;  // frame whose operand block is in LDS (block-uniform)
 
-    // Tile order.  Workgroup b runs on XCD b % 8; with xcd_order each XCD
-    // takes a contiguous eighth of the tiles (pixels close on screen touch
-    // the same grid cells and now share that XCD's L2), else tiles are
-    // strided over all workgroups.  Both are uniform over the workgroup.
+    // Tile order.  Workgroup b runs on XCD b % 8; with xcd_order the tiles go
+    // to the XCDs in strips of kStrip, so that pixels close on screen, which
+    // touch the same grid cells, share an L2, and every XCD gets a like share
+    // of each part of the image (a contiguous eighth of it per XCD took
+    // 181-205 us where strips take 165 and the plain order 169, room
+    // network, 1920x1080, FP16: an eighth may be all sky or all clutter).
+    // Else tiles are strided over all workgroups.  Both are uniform over the
+    // workgroup and ascend.
     const bool by_xcd = a.xcd_order && (gridDim.x % kXcds) == 0;
-    const int64_t per_xcd = (a.n_tiles + kXcds - 1) / kXcds;
-    const int64_t first = by_xcd ? (int64_t)(blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds
-                                 : (int64_t)blockIdx.x;
-    const int64_t last = by_xcd ? (int64_t)(blockIdx.x % kXcds + 1) * per_xcd : a.n_tiles;
-    const int64_t step = by_xcd ? (int64_t)(gridDim.x / kXcds) : (int64_t)gridDim.x;
-    for (int64_t tile = first; tile < last && tile < a.n_tiles; tile += step) {
+    const uint32_t first = by_xcd ? blockIdx.x / kXcds : blockIdx.x;
+    const uint32_t step = by_xcd ? gridDim.x / kXcds : gridDim.x;
+    for (uint32_t i = first;; i += step) {
+        const uint32_t tile = by_xcd ? (i / kStrip * kXcds + blockIdx.x % kXcds) * kStrip + i % kStrip : i;
+        if (tile >= (uint64_t)a.n_tiles) break;   // fewer than 2^27 tiles (16 frames below 2^28 pixels)
         int fi = 0;
         for (int k = 1; k < a.n_frames; ++k)
             if (tile >= ka->f[k].tile_begin) fi = k;
@@ -96,23 +100,23 @@ void k_query(const QueryArgs a)
                 __syncthreads();
                 const u4 *src = reinterpret_cast<const u4 *>(fmodel + kLevelBytes);
                 u4 *dst = reinterpret_cast<u4 *>(smem);
-                for (int k = threadIdx.x; k < O::W_BYTES / 16; k += BLOCK) dst[k] = src[k];
+                for (int k = threadIdx.x; k < O::W_BYTES / 16; k += n_threads) dst[k] = src[k];
                 if constexpr (S::SL) {  // level table behind the weights (per-lane level reads)
                     const u4 *lsrc = reinterpret_cast<const u4 *>(fmodel);
                     u4 *ldst = reinterpret_cast<u4 *>(smem + O::W_BYTES);
-                    for (int k = threadIdx.x; k < kLevelBytes / 16; k += BLOCK) ldst[k] = lsrc[k];
+                    for (int k = threadIdx.x; k < kLevelBytes / 16; k += n_threads) ldst[k] = lsrc[k];
                 }
                 if constexpr (TRAIN && P == NIV_FP16) {  // grid level 0 behind the staging blocks
                     const uint32_t *gsrc = reinterpret_cast<const uint32_t *>(fmodel + a.grid_off) + a.l0_off;
-                    uint32_t *l0 = reinterpret_cast<uint32_t *>(smem + O::W_BYTES) + kWavesPerBlock * 64 * O::ROW_DW;
-                    for (uint32_t k = threadIdx.x; k < a.l0_words; k += BLOCK) l0[k] = gsrc[k];
+                    uint32_t *l0 = reinterpret_cast<uint32_t *>(smem + O::W_BYTES) + n_waves * 64 * O::ROW_DW;
+                    for (uint32_t k = threadIdx.x; k < a.l0_words; k += n_threads) l0[k] = gsrc[k];
                 }
                 __syncthreads();
                 staged = fi;
             }
         }
         const int64_t count = ka->f[fi].count;
-        const int64_t chunk = (tile - ka->f[fi].tile_begin) * kWavesPerBlock + wave;
+        const int64_t chunk = (tile - ka->f[fi].tile_begin) * n_waves + wave;
         if (chunk * 64 >= count) continue;   // this wave has no pixels in the frame's last tile
         const __amdgpu_buffer_rsrc_t grid_rsrc = __builtin_amdgcn_make_buffer_rsrc(
             (void *)(fmodel + a.grid_off), (short)0, (int)a.grid_bytes, 0x00020000);
@@ -412,7 +416,7 @@ void k_query(const QueryArgs a)
                         // volume: level 0 comes from its LDS copy instead of
                         // a gather touching a cache line per lane
                         const uint32_t *l0 = reinterpret_cast<const uint32_t *>(smem + O::W_BYTES) +
-                                             kWavesPerBlock * 64 * O::ROW_DW;
+                                             n_waves * 64 * O::ROW_DW;
                         f = encode_dense_lds<P>(lvs[0], p, l0);
                     } else {
                         f = encode_level_buf<P, F32C>(lvs[l], p, a.hash_mask, grid_rsrc, pf);
