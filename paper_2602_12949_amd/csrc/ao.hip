@@ -29,6 +29,7 @@
 #pragma clang fp contract(off)
 
 #include "mc_device.h"
+#include "wave.h"
 
 namespace niv {
 namespace {
@@ -55,12 +56,15 @@ struct Tri {              // vertex 0 and the two edges from it
 
 constexpr int kLeaf = 4;
 // Stack entries per lane: a ray pushes at most one node per level it
-// descends, so the build keeps the depth within kStack.  20 entries (20 KB
-// of LDS per 256-lane workgroup) let 8 workgroups share a CU, 8 waves per
-// SIMD, which the latency-bound walk needs (32 entries, 5 waves: 8.0 ms
-// instead of 7.0 on the 3840x2160 frame).
+// descends, so the build keeps the depth within kStack, and a launch holds
+// as many as its tree is deep.
 constexpr int kStack = 20;
 constexpr int kAoBlock = 256;
+// Lanes without a ray that make a wave hand out new ones.
+constexpr int kRefill = 8;
+// LDS of one wave: the lanes' stacks, 64 rays ready to be handed out
+// (direction), the pixels' hits and the lanes of the pixels that trace
+constexpr int ao_wave_bytes(int stack) { return stack * 64 * 4 + 3 * 64 * 4 + 64 * 4 + 64; }
 constexpr int64_t kMaxTris = int64_t(kLeaf) << kStack;   // 2^22: the median levels alone fit the stack
 
 struct AoArgs {
@@ -73,25 +77,35 @@ struct AoArgs {
     float lo0[3], hi0[3], lo1[3], hi1[3];   // the root's two boxes (empty without triangles)
     float radius, eps;
     int32_t rays;
+    int32_t stack;             // stack entries per lane (at least the tree's depth)
     uint64_t seed;
 };
 
 // Moller-Trumbore: o + t d = v0 + u e1 + v e2 solved by Cramer's rule; both
-// sides of the triangle count.
+// sides of the triangle count.  Most triangles of a leaf are missed by far:
+// a product with the approximate reciprocal (a few units in the last place
+// off) turns those away, and only the others take the divisions that decide.
 __device__ inline bool tri_hit(const Tri &T, const float o[3], const float d[3], float tmax)
 {
     const float p0 = d[1] * T.e2[2] - d[2] * T.e2[1];
     const float p1 = d[2] * T.e2[0] - d[0] * T.e2[2];
     const float p2 = d[0] * T.e2[1] - d[1] * T.e2[0];
     const float det = T.e1[0] * p0 + T.e1[1] * p1 + T.e1[2] * p2;
-    if (det == 0.0f) return false;
     const float s0 = o[0] - T.v0[0], s1 = o[1] - T.v0[1], s2 = o[2] - T.v0[2];
-    const float u = (s0 * p0 + s1 * p1 + s2 * p2) / det;
-    if (!(u >= 0.0f && u <= 1.0f)) return false;
+    const float un = s0 * p0 + s1 * p1 + s2 * p2;
     const float q0 = s1 * T.e1[2] - s2 * T.e1[1];
     const float q1 = s2 * T.e1[0] - s0 * T.e1[2];
     const float q2 = s0 * T.e1[1] - s1 * T.e1[0];
-    const float v = (d[0] * q0 + d[1] * q1 + d[2] * q2) / det;
+    const float vn = d[0] * q0 + d[1] * q1 + d[2] * q2;
+    // the reciprocal of a tiny determinant is not a normal number: those divide
+    const bool tiny = !(fabsf(det) > 1e-30f);
+    const float r = __builtin_amdgcn_rcpf(det), ua = un * r, va = vn * r;
+    const bool far = ua < -1e-4f || va < -1e-4f || ua + va > 1.0f + 1e-4f;
+    if (far && !tiny) return false;
+    if (det == 0.0f) return false;
+    const float u = un / det;
+    if (!(u >= 0.0f && u <= 1.0f)) return false;
+    const float v = vn / det;
     if (!(v >= 0.0f && u + v <= 1.0f)) return false;
     const float t = (T.e2[0] * q0 + T.e2[1] * q1 + T.e2[2] * q2) / det;
     return t > 0.0f && t <= tmax;
@@ -121,16 +135,39 @@ __device__ inline float box_dist2(const float lo[3], const float hi[3], const fl
     return r2;
 }
 
+// One lane per pixel for the pixel's data and result; the rays of a wave's
+// pixels form one queue that its lanes draw from, whoever's pixel a ray
+// belongs to.  A walk visits 18 inner nodes and 12 triangles on average but
+// up to ~100 of them (two 20,480-triangle spheres), so lanes that walk one
+// ray each and wait for the longest are idle most of the time; here a lane
+// that is done takes the next ray (once kRefill lanes wait), and each step
+// runs what more of the lanes stand at, an inner node or a leaf, instead of
+// both for part of the wave.  64 directions at a time are drawn by all lanes
+// into LDS, since a draw is 64-bit multiplications that a few waiting lanes
+// would make the whole wave execute.  Bound by the
+// vector ALU (0.85 busy); 3840x2160, 16 rays, 40,960 triangles: one ray per
+// lane at a time 5.66 ms, the same after ordering each wave's rays by
+// direction 5.30, nodes and leaves in turn for all lanes 4.68, this 2.40
+// (kRefill 4 and 16: 2.37 and 2.37 where 8 gave 2.31; one triangle per leaf
+// step: 2.6).
 __global__ __launch_bounds__(kAoBlock) void k_dynamic_ao(const AoArgs a)
 {
-    __shared__ int32_t stacks[kStack * kAoBlock];
-    int32_t *stack = stacks + threadIdx.x;   // entry e at stack[e * kAoBlock]
+    extern __shared__ __attribute__((aligned(16))) uint8_t ao_lds[];
+    constexpr int32_t kDone = INT32_MIN;   // the lane has no ray
+    const int lane = threadIdx.x & 63;
+    uint8_t *mine = ao_lds + (threadIdx.x >> 6) * ao_wave_bytes(a.stack);
+    int32_t *stack = reinterpret_cast<int32_t *>(mine) + lane;   // entry e at stack[e * 64]
+    float *ray = reinterpret_cast<float *>(mine + a.stack * 256);
+    uint32_t *nhit = reinterpret_cast<uint32_t *>(ray + 3 * 64);
+    uint8_t *owner = reinterpret_cast<uint8_t *>(nhit + 64);     // lane of the j-th pixel that traces
     const int64_t i = (int64_t)blockIdx.x * kAoBlock + threadIdx.x;
-    if (i >= a.count) return;   // no barriers below
-    const bool use = !a.mask || a.mask[i];
-    float p[3], n[3];
+    const bool in = i < a.count;   // no barriers below
+    const bool use = in && (!a.mask || a.mask[i]);
+    float p[3] = {0.f, 0.f, 0.f}, n[3] = {0.f, 0.f, 0.f};
+    if (in) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) { p[c] = a.pos[3 * i + c]; n[c] = a.nrm[3 * i + c]; }
+        for (int c = 0; c < 3; ++c) { p[c] = a.pos[3 * i + c]; n[c] = a.nrm[3 * i + c]; }
+    }
     const float ln = sqrtf(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
     bool trace = use && ln > 0.0f && __builtin_isfinite(ln);
 #pragma unroll
@@ -138,59 +175,110 @@ __global__ __launch_bounds__(kAoBlock) void k_dynamic_ao(const AoArgs a)
     // a pixel out of reach of both of the root's boxes is visible without tracing
     const float reach = a.radius + a.eps;
     trace = trace && fminf(box_dist2(a.lo0, a.hi0, p), box_dist2(a.lo1, a.hi1, p)) <= reach * reach;
-    float o[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        n[c] /= ln;
-        o[c] = p[c] + a.eps * n[c];
-    }
-    int hits = 0;
-    for (int k = 0; trace && k < a.rays; ++k) {
-        Rng rng(a.seed, (uint64_t)i, (uint64_t)k, 2);
-        float d[3], inv[3], oi[3];
-        cosine_dir(n, rng.u(0), rng.u(1), d);
+    const uint64_t active = __ballot(trace);
+    float vis = 1.0f;
+    if (active) {
+        float po[3];   // ray origin of this lane's pixel
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            inv[c] = d[c] != 0.0f ? 1.0f / d[c] : 1e30f;   // as in the Monte Carlo tracer
-            oi[c] = o[c] * inv[c];
+            n[c] /= ln;
+            po[c] = p[c] + a.eps * n[c];
         }
-        // depth-first from the root: `cur` is the item being visited
-        int sp = 0;
-        int32_t cur = 0;
-        bool hit = false;
+        const int n_active = __popcll(active);
+        if (trace) owner[__popcll(active & ((1ull << lane) - 1ull))] = (uint8_t)lane;
+        nhit[lane] = 0u;
+        wave_lds_fence();
+        const int total = n_active * a.rays;   // ray r: direction r / n_active of pixel r % n_active
+        int base = 0, avail = 0, head = 0;     // rays [base, base + avail) are drawn, the first `head` handed out
+        // the lane's ray
+        int32_t cur = kDone;
+        int sp = 0, px = 0;
+        float o[3], d[3], inv[3], oi[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) o[c] = d[c] = inv[c] = oi[c] = 0.0f;
         while (true) {
-            if (cur >= 0) {           // inner node: both children's boxes
-                const float4 *w = reinterpret_cast<const float4 *>(a.nodes + cur);
-                const float4 w0 = w[0], w1 = w[1], w2 = w[2], w3 = w[3];
-                const float l0[3] = {w0.x, w0.y, w0.z}, h0[3] = {w1.x, w1.y, w1.z};
-                const float l1[3] = {w2.x, w2.y, w2.z}, h1[3] = {w3.x, w3.y, w3.z};
-                const float e0 = box_entry(l0, h0, inv, oi, a.radius);
-                const float e1 = box_entry(l1, h1, inv, oi, a.radius);
-                const int32_t c0 = __builtin_bit_cast(int32_t, w0.w), c1 = __builtin_bit_cast(int32_t, w2.w);
-                if (e0 != INFINITY && e1 != INFINITY) {   // nearer child next, the other later
-                    const bool first0 = e0 <= e1;
-                    if (sp < kStack) {    // always true for trees the host accepted
-                        stack[sp * kAoBlock] = first0 ? c1 : c0;
+            const uint64_t idle = __ballot(cur == kDone);
+            const int n_idle = __popcll(idle);
+            const bool more = base + head < total;
+            if (!more && n_idle == 64) break;
+            if (more && n_idle >= kRefill) {
+                if (head == avail) {   // draw the next 64 rays
+                    base += avail;
+                    head = 0;
+                    avail = min(64, total - base);
+                    const int r = min(base + lane, total - 1);
+                    const int k = r / n_active, own = owner[r - k * n_active];
+                    float pn[3], nd[3];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) pn[c] = __shfl(n[c], own);
+                    Rng rng(a.seed, (uint64_t)(i - lane + own), (uint64_t)k, 2);
+                    cosine_dir(pn, rng.u(0), rng.u(1), nd);
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) ray[c * 64 + lane] = nd[c];
+                    wave_lds_fence();
+                }
+                const int j = head + __popcll(idle & ((1ull << lane) - 1ull));
+                const bool take = cur == kDone && j < avail;
+                const int r = base + min(j, avail - 1), own = owner[r % n_active];
+                float no[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) no[c] = __shfl(po[c], own);
+                if (take) {
+                    px = own;
+                    cur = 0;
+                    sp = 0;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        o[c] = no[c];
+                        d[c] = ray[c * 64 + j];
+                        inv[c] = d[c] != 0.0f ? 1.0f / d[c] : 1e30f;   // as in the Monte Carlo tracer
+                        oi[c] = o[c] * inv[c];
+                    }
+                }
+                head = min(head + n_idle, avail);
+            }
+            const int n_inner = __popcll(__ballot(cur >= 0)), n_leaf = __popcll(__ballot(cur < 0 && cur != kDone));
+            if (n_inner >= n_leaf) {
+                if (cur >= 0) {   // both children's boxes; the nearer child next, the other on the stack
+                    const float4 *w = reinterpret_cast<const float4 *>(a.nodes + cur);
+                    const float4 w0 = w[0], w1 = w[1], w2 = w[2], w3 = w[3];
+                    const float l0[3] = {w0.x, w0.y, w0.z}, h0[3] = {w1.x, w1.y, w1.z};
+                    const float l1[3] = {w2.x, w2.y, w2.z}, h1[3] = {w3.x, w3.y, w3.z};
+                    const float e0 = box_entry(l0, h0, inv, oi, a.radius);
+                    const float e1 = box_entry(l1, h1, inv, oi, a.radius);
+                    const int32_t c0 = __builtin_bit_cast(int32_t, w0.w), c1 = __builtin_bit_cast(int32_t, w2.w);
+                    const bool in0 = e0 != INFINITY, in1 = e1 != INFINITY, first0 = e0 <= e1;
+                    if (in0 && in1 && sp < a.stack) {   // (room: always so for trees the host accepted)
+                        stack[sp * 64] = first0 ? c1 : c0;
                         ++sp;
                     }
-                    cur = first0 ? c0 : c1;
-                    continue;
+                    if (in0 || in1) {
+                        cur = first0 ? c0 : c1;   // a missed child's distance is infinite
+                    } else if (sp == 0) {
+                        cur = kDone;
+                    } else {
+                        --sp;
+                        cur = stack[sp * 64];
+                    }
                 }
-                if (e0 != INFINITY) { cur = c0; continue; }
-                if (e1 != INFINITY) { cur = c1; continue; }
-            } else {                  // leaf: its triangles
+            } else if (cur < 0 && cur != kDone) {   // the leaf's triangles
                 const int32_t code = -1 - cur;
                 const int32_t first = code >> 3, cnt = code & 7;
+                bool hit = false;
                 for (int32_t t = first; t < first + cnt && !hit; ++t) hit = tri_hit(a.tris[t], o, d, a.radius);
-                if (hit) break;
+                if (hit) atomicAdd(&nhit[px], 1u);
+                if (hit || sp == 0) {
+                    cur = kDone;
+                } else {
+                    --sp;
+                    cur = stack[sp * 64];
+                }
             }
-            if (sp == 0) break;
-            --sp;
-            cur = stack[sp * kAoBlock];
         }
-        hits += hit ? 1 : 0;
+        wave_lds_fence();
+        if (trace) vis = 1.0f - (float)nhit[lane] / (float)a.rays;
     }
-    const float vis = trace ? 1.0f - (float)hits / (float)a.rays : 1.0f;
+    if (!in) return;
     if (a.vis) a.vis[i] = vis;
     if (use && vis != 1.0f) {
 #pragma unroll
@@ -483,8 +571,10 @@ niv_status niv_ao_apply(const niv_ao *ao, const niv_ao_params *p, int64_t count,
     a.eps = p->eps;
     a.rays = p->rays;
     a.seed = p->seed;
+    a.stack = std::max(1, ao->depth);
     const int64_t blocks = (count + kAoBlock - 1) / kAoBlock;
-    hipLaunchKernelGGL(k_dynamic_ao, dim3((unsigned)blocks), dim3(kAoBlock), 0, stream, a);
+    hipLaunchKernelGGL(k_dynamic_ao, dim3((unsigned)blocks), dim3(kAoBlock),
+                       (size_t)(kAoBlock / 64) * ao_wave_bytes(a.stack), stream, a);
     return hs(hipGetLastError());
 }
 

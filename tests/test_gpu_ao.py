@@ -143,3 +143,36 @@ def test_room_4k_6d_full_size(rays, workload_gbuffer):
     _compare(vis[sel], ref, rays)
     far = np.setdiff1d(np.flatnonzero(mask), near)
     assert np.all(vis[far] == 1.0)
+
+
+# a wave's queue of rays: fewer pixels than lanes, rays that do not fill or
+# that cross the 64 drawn at a time, a tree that is one leaf, one inner node
+# or a few levels
+@pytest.mark.parametrize("count,rays", [(1, 1), (1, 65), (3, 64), (63, 3), (64, 1), (65, 17), (300, 5)])
+@pytest.mark.parametrize("n_tris", [1, 5, 40])
+def test_ray_queue_edges(count, rays, n_tris):
+    rng = np.random.default_rng(100 * count + rays + n_tris)
+    tris = (rng.uniform(-1, 1, (n_tris, 1, 3)) + rng.uniform(-0.6, 0.6, (n_tris, 3, 3))).astype(np.float32)
+    pos = rng.uniform(-1, 1, (count, 3)).astype(np.float32)
+    nrm = rng.standard_normal((count, 3)).astype(np.float32)
+    mask = (rng.uniform(size=count) < 0.7).astype(np.uint8)
+    mask[0] = 1
+    vis = _ao(tris).apply(_t(pos), _t(nrm), rays, 2.0, EPS, seed=31, mask=_t(mask)).cpu().numpy()
+    assert np.all(vis[mask == 0] == 1.0)
+    sel = np.flatnonzero(mask)
+    ref = O.dynamic_ao(tris, pos[sel], nrm[sel], rays, 2.0, EPS, 31, point_id=sel)
+    hg = np.rint((1.0 - vis[sel].astype(np.float64)) * rays).astype(np.int64)
+    ho = np.rint((1.0 - ref) * rays).astype(np.int64)
+    assert np.abs(hg - ho).max() <= 1 and np.abs(hg - ho).sum() <= 1 + 0.005 * rays * len(sel)
+
+
+def test_tiny_triangles_keep_the_dividing_test():
+    """Determinants below the reciprocal's range: a fan of triangles 1e-16
+    across a point straight ahead, a quad of ordinary size behind it."""
+    quad = np.array([[[-1, -1, 1], [1, -1, 1], [1, 1, 1]], [[-1, -1, 1], [1, 1, 1], [-1, 1, 1]]], np.float32)
+    tiny = (np.array([[0, 0, 0], [1, 0, 0], [0, 1, 0]]) * 1e-16 + np.array([0, 0, 0.5])).astype(np.float32)
+    flat = np.zeros((1, 3, 3), np.float32)
+    tris = np.concatenate([quad, tiny[None], flat]).astype(np.float32)
+    pos, nrm = np.zeros((2, 3), np.float32), np.array([[0, 0, 1], [0.2, 0, 1]], np.float32)
+    vis = _ao(tris).apply(_t(pos), _t(nrm), 1024, 10.0, 0.0, seed=9).cpu().numpy()
+    _compare(vis, O.dynamic_ao(tris, pos, nrm, 1024, 10.0, 0.0, 9), 1024)
