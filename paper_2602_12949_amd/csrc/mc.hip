@@ -18,6 +18,7 @@
 #pragma clang fp contract(off)
 
 #include "mc_device.h"
+#include "wave.h"
 
 namespace niv {
 
@@ -40,6 +41,7 @@ constexpr int kMaxLights = 8;
 struct Hit {
     float t;
     int prim;
+    int own;        // its place in the trace list (scenes with candidates), else -1
     float n[3];
     bool back;
 };
@@ -102,12 +104,83 @@ struct __attribute__((aligned(32))) TraceRec {
 static_assert(sizeof(TraceRec) == 32, "trace record is 32 bytes");
 typedef const __attribute__((address_space(4))) TraceRec *ConstRecs;
 
+// Candidates of a ray in a static scene of at most 64 primitives.  A scan
+// tests 40 primitives (~21 vector operations a box) for a ray that can meet
+// two or three of them, and the estimator is bound by the vector ALU.  So the scene's
+// bounds are cut into cells, and per cell there are the primitives (bits in
+// the order of the trace list) that a ray from it can meet, one mask per bin
+// of directions, and those that can stand between it and a light, one mask
+// per light.  The masks are conservative (built from intervals widened by
+// far more than the tracer's rounding), so a ray that tests only its
+// candidates finds the hit that a scan finds, bit for bit.  A wave takes as
+// many steps as its lane with the most candidates: 5 towards a light, 7 to 12
+// in any direction with the cells and bins below (room of 32 boxes).
+// 2^17 points x 256 samples x 3 bounces: 9.10 -> 5.19 ms (4 x 4 bins 5.45,
+// 8 x 8 5.12; 14 cells 5.38, 28 cells 5.12, for twice the table).
+constexpr int kCullPrims = 64;
+constexpr int kCullAxis = 20;              // cells along the longest axis
+constexpr int kCullG = 6;                  // direction bins per edge of a cube face
+constexpr int kCullBins = 6 * kCullG * kCullG;
+constexpr int kCullMinBoxes = 8;           // fewer boxes are scanned
+struct CullGrid {
+    float lo[3], inv[3];                   // cell = (p - lo) * inv
+    int32_t n[3];
+    int32_t stride;                        // masks of a cell: the bins', then the lights'
+    uint64_t kind[5];                      // masks of the boxes, the rectangles by axis, the disks
+    int32_t skip_own;                      // a ray need not test the surface that it leaves
+    int32_t pad;
+    double cell[3], origin[3], margin;     // what the build reads
+};
+typedef const __attribute__((address_space(4))) CullGrid *ConstCull;
+
 struct SceneRefs {
     ConstPrims prims;
     int32_t n_prims;
     ConstRecs recs;        // null: test every primitive in order (moving scenes)
     int32_t nb, nr[3], nd;
+    ConstCull cull;        // null: scan the whole list
+    const uint64_t *masks; // [cell][stride]
+    const TraceRec *lrec;  // the trace list in LDS (with cull); pad: place in the list
 };
+
+// Where rays start: the masks of the cell (null outside the cells) and the
+// primitives that they may meet at all.  A ray that leaves a surface on its
+// front side, eps off it, cannot meet that rectangle or convex box again.
+struct CullStart {
+    const uint64_t *cell;
+    uint64_t all;
+    __device__ uint64_t mask(int m) const { return cell ? cell[m] & all : all; }
+};
+__device__ inline CullStart cull_start(const SceneRefs &sc, const float p[3], int own)
+{
+    int32_t c[3];
+    bool in = true;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float f = (p[a] - sc.cull->lo[a]) * sc.cull->inv[a];
+        in = in && f >= 0.0f && f < (float)sc.cull->n[a];
+        c[a] = in ? (int32_t)f : 0;
+    }
+    const int64_t cell = c[0] + sc.cull->n[0] * (c[1] + sc.cull->n[1] * c[2]);
+    CullStart s;
+    s.cell = in ? sc.masks + cell * sc.cull->stride : nullptr;
+    s.all = (own >= 0 && sc.cull->skip_own) ? ~(1ull << own) : ~0ull;
+    return s;
+}
+
+// Bin of a direction: the face of the cube that it leaves through (its
+// largest component), cut kCullG x kCullG by the ratios of the others to it.
+__device__ inline int cull_bin(const float d[3])
+{
+    const float ax = fabsf(d[0]), ay = fabsf(d[1]), az = fabsf(d[2]);
+    const int a = (ax >= ay && ax >= az) ? 0 : (ay >= az ? 1 : 2);
+    const float m = a == 0 ? d[0] : a == 1 ? d[1] : d[2];
+    const float u = a == 0 ? d[1] : a == 1 ? d[2] : d[0], v = a == 0 ? d[2] : a == 1 ? d[0] : d[1];
+    const float r = __builtin_amdgcn_rcpf(fabsf(m));
+    const int iu = min(max((int)((u * r + 1.0f) * (0.5f * kCullG)), 0), kCullG - 1);
+    const int iv = min(max((int)((v * r + 1.0f) * (0.5f * kCullG)), 0), kCullG - 1);
+    return ((2 * a + (m < 0.0f ? 1 : 0)) * kCullG + iu) * kCullG + iv;
+}
 
 // the ray origin moved by -shift (a primitive translated by shift is tested
 // with the translated ray: same distance, side and normal)
@@ -231,11 +304,154 @@ __device__ inline void trace_list(const SceneRefs &sc, const Ray &r, float &best
     }
 }
 
+// The candidates of one ray, per lane, with the arithmetic and the tie rule
+// of trace_list (bits ascend in the order of the list).
+template <int A>
+__device__ inline bool rect_rec_test(const TraceRec &q, const Ray &r, float &t)
+{
+    constexpr int U = A == 2 ? 0 : A + 1, V = A == 0 ? 2 : A - 1;
+    t = slab(q.a[A], r, A);
+    const float hu = __builtin_fmaf(t, r.d[U], r.o[U]), hv = __builtin_fmaf(t, r.d[V], r.o[V]);
+    return (t > 0.0f) && (fabsf(hu - q.a[U]) <= q.b[0]) && (fabsf(hv - q.a[V]) <= q.b[1]);
+}
+__device__ inline bool box_rec_test(const TraceRec &q, const Ray &r, float &t, bool &front)
+{
+    const float x1 = slab(q.a[0], r, 0), x2 = slab(q.b[0], r, 0);
+    const float y1 = slab(q.a[1], r, 1), y2 = slab(q.b[1], r, 1);
+    const float z1 = slab(q.a[2], r, 2), z2 = slab(q.b[2], r, 2);
+    const float tn = fmaxf(fmaxf(fminf(x1, x2), fminf(y1, y2)), fminf(z1, z2));
+    const float tf = fminf(fminf(fmaxf(x1, x2), fmaxf(y1, y2)), fmaxf(z1, z2));
+    front = tn > 0.0f;
+    t = front ? tn : tf;
+    return (tn <= tf) && (tf > 0.0f);
+}
+__device__ inline bool disk_test(ConstPrims pd, const Ray &r, float &t, float &den)
+{
+    const float nx = pd->q[0], ny = pd->q[1], nz = pd->q[2];
+    den = r.d[0] * nx + r.d[1] * ny + r.d[2] * nz;
+    t = ((pd->p[0] - r.o[0]) * nx + (pd->p[1] - r.o[1]) * ny + (pd->p[2] - r.o[2]) * nz) / den;
+    float r2 = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const float e = __builtin_fmaf(t, r.d[c], r.o[c]) - pd->p[c];
+        r2 = __builtin_fmaf(e, e, r2);
+    }
+    return (den != 0.0f) && (t > 0.0f) && (r2 <= pd->radius * pd->radius);
+}
+
+// f(k) for each set bit of the lane's mask until it returns true; the halves
+// apart, so that a step costs 32-bit operations and the boxes, which come
+// first, are mostly in one.
+template <class F> __device__ __forceinline__ bool any_bit(uint64_t mask, F &&f)
+{
+    bool stop = false;
+    uint32_t m = (uint32_t)mask;
+    while (m) {
+        stop = f(__builtin_ctz(m));
+        m = stop ? 0u : m & (m - 1u);
+    }
+    m = stop ? 0u : (uint32_t)(mask >> 32);
+    while (m) {
+        stop = f(32 + __builtin_ctz(m));
+        m = stop ? 0u : m & (m - 1u);
+    }
+    return stop;
+}
+
+// Closest hit among the candidates; bk: its place in the list.
+__device__ inline void trace_mask(const SceneRefs &sc, uint64_t mask, const Ray &r, float &best, int &bp, bool &bback,
+                                  int &bk)
+{
+    // index and place in one word: the order of the words is that of the indices
+    int code = INT32_MAX;
+    any_bit(mask & sc.cull->kind[0], [&](int k) {
+        const TraceRec q = sc.lrec[k];
+        float t;
+        bool front;
+        const bool take = box_rec_test(q, r, t, front) && (t < best);
+        best = take ? t : best;
+        code = take ? q.pad : code;
+        bback = take ? !front : bback;
+        return false;
+    });
+    auto rects = [&](auto axis) {
+        constexpr int A = decltype(axis)::value;
+        any_bit(mask & sc.cull->kind[1 + A], [&](int k) {
+            const TraceRec q = sc.lrec[k];
+            float t;
+            const bool take = rect_rec_test<A>(q, r, t) && ((t < best) || ((t == best) && (q.pad < code)));
+            best = take ? t : best;
+            code = take ? q.pad : code;
+            bback = take ? (r.d[A] * q.b[2] > 0.0f) : bback;
+            return false;
+        });
+    };
+    rects(std::integral_constant<int, 0>());
+    rects(std::integral_constant<int, 1>());
+    rects(std::integral_constant<int, 2>());
+    any_bit(mask & sc.cull->kind[4], [&](int k) {
+        const int c = sc.lrec[k].pad;
+        float t, den;
+        const bool take = disk_test(sc.prims + (c >> 8), r, t, den) && ((t < best) || ((t == best) && (c < code)));
+        best = take ? t : best;
+        code = take ? c : code;
+        bback = take ? (den > 0.0f) : bback;
+        return false;
+    });
+    bp = code != INT32_MAX ? code >> 8 : -1;
+    bk = code & 0xff;
+}
+
+// Whether light lk is the closest hit of the ray: it is hit, and no candidate
+// is hit before it (or at its distance with a lower index).
+__device__ inline bool sees_light(const SceneRefs &sc, uint64_t mask, const Ray &r, int lk)
+{
+    float tl;
+    bool seen;
+    if (sc.prims[lk].kind == 1) {
+        const int a = sc.prims[lk].axis;
+        TraceRec q;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) q.a[c] = sc.prims[lk].p[c];
+        q.b[0] = sc.prims[lk].q[0];
+        q.b[1] = sc.prims[lk].q[1];
+        seen = a == 0 ? rect_rec_test<0>(q, r, tl) : a == 1 ? rect_rec_test<1>(q, r, tl) : rect_rec_test<2>(q, r, tl);
+    } else {
+        float den;
+        seen = disk_test(sc.prims + lk, r, tl, den);
+    }
+    if (!seen) mask = 0ull;
+    auto before = [&](float t, int id) { return (t < tl) || ((t == tl) && (id < lk)); };
+    bool stop = any_bit(mask & sc.cull->kind[0], [&](int k) {
+        const TraceRec q = sc.lrec[k];
+        float t;
+        bool front;
+        return box_rec_test(q, r, t, front) && before(t, q.idx);
+    });
+    auto rects = [&](auto axis) {
+        constexpr int A = decltype(axis)::value;
+        stop |= any_bit(stop ? 0ull : mask & sc.cull->kind[1 + A], [&](int k) {
+            const TraceRec q = sc.lrec[k];
+            float t;
+            return rect_rec_test<A>(q, r, t) && before(t, q.idx);
+        });
+    };
+    rects(std::integral_constant<int, 0>());
+    rects(std::integral_constant<int, 1>());
+    rects(std::integral_constant<int, 2>());
+    stop |= any_bit(stop ? 0ull : mask & sc.cull->kind[4], [&](int k) {
+        const int id = sc.lrec[k].idx;
+        float t, den;
+        return disk_test(sc.prims + id, r, t, den) && before(t, id);
+    });
+    return seen && !stop;
+}
+
 // MOVING: the scene changes with the point's scene variable tv (uniform over
 // the wave): primitive k is translated by tv * motion[k] (motion[k].w != 0
 // marks a moving primitive).
 template <bool MOVING>
-__device__ inline bool trace(const SceneRefs &sc, const float o[3], const float d[3],
+__device__ inline bool trace(const SceneRefs &sc, const CullStart &from, const float o[3], const float d[3],
                              Hit &h, ConstMotion motion = nullptr, float tv = 0.0f)
 {
     ConstPrims prims = sc.prims;
@@ -243,7 +459,10 @@ __device__ inline bool trace(const SceneRefs &sc, const float o[3], const float 
     float best = INFINITY;
     int bp = -1;
     bool bback = false;
-    if (!MOVING && sc.recs) {
+    int own = -1;
+    if (!MOVING && sc.cull) {
+        trace_mask(sc, from.mask(cull_bin(d)), r, best, bp, bback, own);
+    } else if (!MOVING && sc.recs) {
         trace_list(sc, r, best, bp, bback);
     } else {
         for (int k = 0; k < sc.n_prims; ++k) {
@@ -256,6 +475,7 @@ __device__ inline bool trace(const SceneRefs &sc, const float o[3], const float 
     }
     h.t = best;
     h.prim = bp;
+    h.own = own;
     h.back = bback;
     h.n[0] = h.n[1] = h.n[2] = 0.0f;
     if (bp < 0) return false;
@@ -323,6 +543,7 @@ struct McArgs {
     const Prim *prims;
     const TraceRec *recs;     // trace list of the static scene
     int32_t nb, nr[3], nd;
+    const CullGrid *cull;     // candidates of the static scene, or null
     const int32_t *lights;
     const Motion4 *motion;    // [n_prims] (x, y, z, moving) or null
     const float *t;           // [count] scene variable per point or null (0)
@@ -338,9 +559,9 @@ struct McArgs {
     uint8_t *out_valid;
 };
 
-// Next-event estimate at y with normal ny toward light j: L cos cos / d^2 A.
+// Next-event estimate at y with normal ny toward light j (primitive lk): L cos cos / d^2 A.
 template <bool MOVING>
-__device__ inline bool nee(const SceneRefs &sc, int lk, const float oy[3],
+__device__ inline bool nee(const SceneRefs &sc, const CullStart &from, int j, int lk, const float oy[3],
                            const float ny[3], float u1, float u2, float &G, ConstMotion motion,
                            float tv)
 {
@@ -356,8 +577,12 @@ __device__ inline bool nee(const SceneRefs &sc, int lk, const float oy[3],
     float cy = ny[0] * w[0] + ny[1] * w[1] + ny[2] * w[2];
     float cq = -(nq[0] * w[0] + nq[1] * w[1] + nq[2] * w[2]);
     if (cy <= 0.0f || cq <= 0.0f) return false;
-    Hit hh;
-    if (!trace<MOVING>(sc, oy, w, hh, motion, tv) || hh.prim != lk) return false;
+    if (!MOVING && sc.cull) {
+        if (!sees_light(sc, from.mask(kCullBins + j), make_ray(oy, w), lk)) return false;
+    } else {
+        Hit hh;
+        if (!trace<MOVING>(sc, from, oy, w, hh, motion, tv) || hh.prim != lk) return false;
+    }
     G = cy * cq / d2 * A;
     return true;
 }
@@ -385,18 +610,20 @@ __device__ inline void mc_point(const SceneRefs &sc, ConstInts lights, int J, fl
         float o[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) o[c] = px[c] + eps * pn[c];
+        CullStart from = {nullptr, ~0ull};
+        if (!MOVING && sc.cull) from = cull_start(sc, o, -1);
         if (flags & 8) {  // direct irradiance at x by light sampling (test mode)
             for (int j = 0; j < J; ++j) {
                 int lk = lights[j];
                 float G;
-                if (nee<MOVING>(sc, lk, o, pn, rng.u(2 * j), rng.u(2 * j + 1), G, motion, tv))
+                if (nee<MOVING>(sc, from, j, lk, o, pn, rng.u(2 * j), rng.u(2 * j + 1), G, motion, tv))
                     for (int c = 0; c < 3; ++c) val[c] += prims[lk].emission[c] * G;
             }
         } else {
             float d[3];
             cosine_dir(pn, rng.u(0), rng.u(1), d);
             Hit h;
-            bool ok = trace<MOVING>(sc, o, d, h, motion, tv);
+            bool ok = trace<MOVING>(sc, from, o, d, h, motion, tv);
             if (ok && h.back) { backs++; ok = false; }
             if (ok) {
                 float rad[3] = {0.f, 0.f, 0.f};
@@ -411,11 +638,12 @@ __device__ inline void mc_point(const SceneRefs &sc, ConstInts lights, int J, fl
                     const int base = 2 + (k - 1) * stride;
                     float oy[3];
                     for (int c = 0; c < 3; ++c) oy[c] = y[c] + eps * ny[c];
+                    if (!MOVING && sc.cull) from = cull_start(sc, oy, h.own);
                     if (flags & 1) {
                         for (int j = 0; j < J; ++j) {
                             int lk = lights[j];
                             float G;
-                            if (nee<MOVING>(sc, lk, oy, ny, rng.u(base + 2 * j), rng.u(base + 2 * j + 1), G,
+                            if (nee<MOVING>(sc, from, j, lk, oy, ny, rng.u(base + 2 * j), rng.u(base + 2 * j + 1), G,
                                             motion, tv))
                                 for (int c = 0; c < 3; ++c)
                                     rad[c] += beta[c] * rho[c] * 0.318309886183790672f * prims[lk].emission[c] * G;
@@ -426,7 +654,7 @@ __device__ inline void mc_point(const SceneRefs &sc, ConstInts lights, int J, fl
                     for (int c = 0; c < 3; ++c) beta[c] *= rho[c];
                     if (beta[0] == 0.f && beta[1] == 0.f && beta[2] == 0.f) break;
                     cosine_dir(ny, rng.u(base + 2 * J), rng.u(base + 2 * J + 1), d);
-                    if (!trace<MOVING>(sc, oy, d, h, motion, tv) || h.back) break;
+                    if (!trace<MOVING>(sc, from, oy, d, h, motion, tv) || h.back) break;
                     if (flags & 2)
                         for (int c = 0; c < 3; ++c) rad[c] += beta[c] * prims[h.prim].emission[c];
                     for (int c = 0; c < 3; ++c) { y[c] = oy[c] + h.t * d[c]; ny[c] = h.n[c]; }
@@ -451,11 +679,32 @@ __device__ inline void mc_point(const SceneRefs &sc, ConstInts lights, int J, fl
     }
 }
 
+// The candidates of a scene for this wave: its trace list in LDS.
+__device__ inline void use_cull(SceneRefs &sc, const CullGrid *cull, TraceRec *lrec, int lane)
+{
+    sc.cull = (ConstCull)cull;
+    sc.masks = reinterpret_cast<const uint64_t *>(cull + 1);
+    sc.lrec = lrec;
+    if (!cull) return;
+    const int n = sc.nb + sc.nr[0] + sc.nr[1] + sc.nr[2] + sc.nd;
+    wave_lds_fence();
+    if (lane < n) {
+        TraceRec q;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) { q.a[c] = sc.recs[lane].a[c]; q.b[c] = sc.recs[lane].b[c]; }
+        q.idx = sc.recs[lane].idx;
+        q.pad = q.idx << 8 | lane;
+        lrec[lane] = q;
+    }
+    wave_lds_fence();
+}
+
 template <bool MOVING>
 __global__ __launch_bounds__(256) void k_mc_irradiance(const McArgs a)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    __shared__ TraceRec lrec[MOVING ? 1 : 4 * kCullPrims];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t i = (int64_t)blockIdx.x * 4 + wave;
     if (i >= a.count) return;  // whole wave leaves together
     SceneRefs sc;
     sc.prims = (ConstPrims)a.prims;
@@ -464,6 +713,7 @@ __global__ __launch_bounds__(256) void k_mc_irradiance(const McArgs a)
     sc.nb = a.nb;
     sc.nr[0] = a.nr[0]; sc.nr[1] = a.nr[1]; sc.nr[2] = a.nr[2];
     sc.nd = a.nd;
+    use_cull(sc, MOVING ? nullptr : a.cull, lrec + (MOVING ? 0 : wave * kCullPrims), lane);
     ConstInts lights = (ConstInts)a.lights;
     const float px[3] = {a.x[3 * i], a.x[3 * i + 1], a.x[3 * i + 2]};
     const float pn[3] = {a.nrm[3 * i], a.nrm[3 * i + 1], a.nrm[3 * i + 2]};
@@ -496,6 +746,7 @@ __global__ __launch_bounds__(256) void k_mc_fallback(const FbArgs a)
 {
     typedef const __attribute__((address_space(4))) FbArgs *ConstFb;
     ConstFb ka = (ConstFb)__builtin_amdgcn_kernarg_segment_ptr();
+    __shared__ TraceRec lrec[4 * kCullPrims];
     const int lane = threadIdx.x & 63;
     const uint32_t n = *a.count < a.cap ? *a.count : a.cap;
     for (uint32_t e = blockIdx.x * 4 + (threadIdx.x >> 6); e < n; e += gridDim.x * 4) {
@@ -510,6 +761,9 @@ __global__ __launch_bounds__(256) void k_mc_fallback(const FbArgs a)
         sc.nb = ka->f[fi].nk[0];
         sc.nr[0] = ka->f[fi].nk[1]; sc.nr[1] = ka->f[fi].nk[2]; sc.nr[2] = ka->f[fi].nk[3];
         sc.nd = ka->f[fi].nk[4];
+        // (a frame whose scene moves traces without the candidates)
+        use_cull(sc, MOVING && ka->f[fi].motion ? nullptr : static_cast<const CullGrid *>(ka->f[fi].cull),
+                 lrec + (threadIdx.x >> 6) * kCullPrims, lane);
         ConstInts lights = (ConstInts)ka->f[fi].lights;
         const float *pos = ka->f[fi].pos, *nrm = ka->f[fi].nrm;
         const float px[3] = {pos[3 * q], pos[3 * q + 1], pos[3 * q + 2]};
@@ -606,6 +860,87 @@ __global__ __launch_bounds__(256) void k_sample_points(const SampleArgs a)
     if (a.out_t) a.out_t[i] = rng.u(7);
 }
 
+// One mask per thread (see CullGrid).  Cells and primitives are widened by
+// the margin, bins by 1e-3: the tracer's rounding is of the order of 1e-6 of
+// the scene, a hundredth of the margin.
+__global__ __launch_bounds__(256) void k_build_cull(CullGrid *grid, const Prim *prims, const TraceRec *recs, int n_prims,
+                                                    const int32_t *lights)
+{
+    const CullGrid g = *grid;
+    uint64_t *masks = reinterpret_cast<uint64_t *>(grid + 1);
+    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t cell = id / g.stride;
+    const int m = (int)(id - cell * g.stride);
+    if (cell >= (int64_t)g.n[0] * g.n[1] * g.n[2]) return;
+    const int ci[3] = {(int)(cell % g.n[0]), (int)(cell / g.n[0] % g.n[1]), (int)(cell / g.n[0] / g.n[1])};
+    double c0[3], c1[3];
+    for (int a = 0; a < 3; ++a) {
+        c0[a] = g.origin[a] + g.cell[a] * ci[a] - g.margin;
+        c1[a] = g.origin[a] + g.cell[a] * (ci[a] + 1) + g.margin;
+    }
+    auto bounds = [&](const Prim &p, double b0[3], double b1[3]) {
+        for (int a = 0; a < 3; ++a) {
+            double h = 0.0;
+            if (p.kind == 1) h = a == (p.axis + 1) % 3 ? p.q[0] : a == (p.axis + 2) % 3 ? p.q[1] : 0.0;
+            if (p.kind == 2) h = p.radius;
+            b0[a] = p.kind == 0 ? p.p[a] : p.p[a] - h;
+            b1[a] = p.kind == 0 ? p.q[a] : p.p[a] + h;
+            b0[a] = (b0[a] < b1[a] ? b0[a] : b1[a]) - g.margin;
+            b1[a] = (b0[a] < b1[a] ? b1[a] : b0[a]) + g.margin;
+        }
+    };
+    // limit k: x + s w <= 0, with w (and its reciprocal) the thread's own
+    double w[6], rw[6];
+    const bool bin = m < kCullBins;
+    const int iv = m % kCullG, iu = m / kCullG % kCullG, face = m / (kCullG * kCullG);
+    const int a = face / 2 % 3, u = (a + 1) % 3, v = (a + 2) % 3;
+    const bool neg = face & 1;
+    if (bin) {
+        // origin o in the cell, direction with the bin's slopes: at the
+        // distance s along the largest axis it is at o + s slope
+        const double step = 2.0 / kCullG, eps = 1e-3;
+        w[0] = iu * step - 1.0 - eps;
+        w[1] = -((iu + 1) * step - 1.0 + eps);
+        w[2] = iv * step - 1.0 - eps;
+        w[3] = -((iv + 1) * step - 1.0 + eps);
+        w[4] = w[5] = 0.0;
+    } else {
+        // the segments from the cell to the light: (1 - s) cell + s light
+        double l0[3], l1[3];
+        bounds(prims[lights[m - kCullBins]], l0, l1);
+        for (int c = 0; c < 3; ++c) {
+            w[2 * c] = l0[c] - c0[c];
+            w[2 * c + 1] = c1[c] - l1[c];
+        }
+    }
+    for (int k = 0; k < 6; ++k) rw[k] = w[k] != 0.0 ? 1.0 / w[k] : 0.0;
+    uint64_t mask = 0ull;
+    for (int k = 0; k < n_prims; ++k) {
+        double b0[3], b1[3], s0 = 0.0, s1 = 1.0;
+        bounds(prims[recs[k].idx], b0, b1);
+        auto below = [&](int i, double x) {   // narrows [s0, s1] by limit i
+            if (w[i] > 0.0) s1 = fmin(s1, -x * rw[i]);
+            else if (w[i] < 0.0) s0 = fmax(s0, -x * rw[i]);
+            else if (x > 0.0) s1 = -INFINITY;
+        };
+        if (bin) {
+            s0 = fmax(0.0, neg ? c0[a] - b1[a] : b0[a] - c1[a]);
+            s1 = neg ? c1[a] - b0[a] : b1[a] - c0[a];
+            below(0, c0[u] - b1[u]);
+            below(1, b0[u] - c1[u]);
+            below(2, c0[v] - b1[v]);
+            below(3, b0[v] - c1[v]);
+        } else {
+            for (int c = 0; c < 3; ++c) {
+                below(2 * c, c0[c] - b1[c]);
+                below(2 * c + 1, b0[c] - c1[c]);
+            }
+        }
+        if (s0 <= s1) mask |= 1ull << k;
+    }
+    masks[id] = mask;
+}
+
 }  // namespace niv
 
 using namespace niv;
@@ -617,6 +952,7 @@ struct mc_scene {
     double *d_cdf = nullptr;
     Motion4 *d_motion = nullptr;   // per primitive (x, y, z, moving), or null: static scene
     TraceRec *d_recs = nullptr;    // trace list: boxes, rectangles by axis, disks
+    CullGrid *d_cull = nullptr;    // candidates (the grid, then its masks), or null
     int32_t nk[5] = {0, 0, 0, 0, 0};  // their counts (boxes, rectangles x/y/z, disks)
     int32_t n_prims = 0, n_lights = 0, n_faces = 0;
     double total_area = 0.0;
@@ -636,9 +972,10 @@ void mc_scene_device_view(const struct mc_scene *s, const void **prims, const in
     *motion = s ? s->d_motion : nullptr;
 }
 
-void mc_scene_trace_view(const struct mc_scene *s, const void **recs, int32_t nk[5])
+void mc_scene_trace_view(const struct mc_scene *s, const void **recs, int32_t nk[5], const void **cull)
 {
     *recs = s ? s->d_recs : nullptr;
+    *cull = s ? s->d_cull : nullptr;
     for (int k = 0; k < 5; ++k) nk[k] = s ? s->nk[k] : 0;
 }
 
@@ -675,6 +1012,7 @@ void release(mc_scene *s)
     (void)hipFree(s->d_cdf);
     (void)hipFree(s->d_motion);
     (void)hipFree(s->d_recs);
+    (void)hipFree(s->d_cull);
     delete s;
 }
 
@@ -714,6 +1052,60 @@ niv_status upload_trace_list(mc_scene *s)
         st = hs(hipMemcpy(s->d_recs, all.data(), sizeof(TraceRec) * all.size(), hipMemcpyHostToDevice));
     return st;
 }
+// Candidates of a static scene (CullGrid).  Nothing is lost without them, so
+// a scene that is too large for the masks, has few boxes, or whose table
+// cannot be allocated is scanned.
+void build_cull(mc_scene *s, const double lo[3], const double hi[3])
+{
+    if (s->n_prims > kCullPrims || s->nk[0] < kCullMinBoxes) return;
+    double extent = 0.0;
+    for (int c = 0; c < 3; ++c) extent = fmax(extent, hi[c] - lo[c]);
+    if (!(extent > 0.0) || !isfinite(extent)) return;
+    CullGrid g;
+    memset(&g, 0, sizeof(g));
+    // rays start up to eps off the surfaces: the cells reach a little further
+    g.margin = 1e-4 * extent;
+    int64_t cells = 1;
+    for (int c = 0; c < 3; ++c) {
+        g.origin[c] = lo[c] - 4.0 * g.margin;
+        const double len = hi[c] - lo[c] + 8.0 * g.margin;
+        g.n[c] = (int32_t)fmin(kCullAxis, fmax(1.0, ceil(len / extent * kCullAxis)));
+        g.cell[c] = len / g.n[c];
+        g.lo[c] = (float)g.origin[c];
+        g.inv[c] = (float)(1.0 / g.cell[c]);
+        cells *= g.n[c];
+    }
+    g.stride = kCullBins + s->n_lights;
+    // eps (1e-4 of the extent) off a surface is well off it in FP32 unless the
+    // scene lies far from the origin
+    double far = 0.0;
+    for (int c = 0; c < 3; ++c) far = fmax(far, fmax(fabs(lo[c]), fabs(hi[c])));
+    g.skip_own = far <= 20.0 * extent ? 1 : 0;
+    int first = 0;
+    for (int l = 0; l < 5; ++l) {
+        for (int k = 0; k < s->nk[l]; ++k) g.kind[l] |= 1ull << (first + k);
+        first += s->nk[l];
+    }
+    const size_t bytes = sizeof(CullGrid) + (size_t)(cells * g.stride) * sizeof(uint64_t);
+    if (hipMalloc(&s->d_cull, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        s->d_cull = nullptr;
+        return;
+    }
+    hipError_t e = hipMemcpy(s->d_cull, &g, sizeof(g), hipMemcpyHostToDevice);
+    if (e == hipSuccess) {
+        const int64_t n = cells * g.stride;
+        hipLaunchKernelGGL(k_build_cull, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, nullptr, s->d_cull, s->d_prims,
+                           s->d_recs, s->n_prims, s->d_lights);
+        e = hipGetLastError();
+        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    }
+    if (e != hipSuccess) {
+        (void)hipFree(s->d_cull);
+        s->d_cull = nullptr;
+    }
+}
+
 // Cumulative-area table of the sampler's surfaces: every rectangle and box
 // face that does not emit and does not move.
 niv_status upload_faces(mc_scene *s, const float *motion)
@@ -808,6 +1200,7 @@ niv_status mc_scene_create(const niv_mc_prim *prims, int32_t n_prims, mc_scene *
         if (st == NIV_OK) st = hs(hipMemcpy(s->d_lights, lights, sizeof(int32_t) * kMaxLights, hipMemcpyHostToDevice));
         if (st == NIV_OK) st = upload_faces(s, nullptr);
         if (st == NIV_OK) st = upload_trace_list(s);
+        if (st == NIV_OK) build_cull(s, lo, hi);
     }
     if (st != NIV_OK) {
         release(s);
@@ -861,6 +1254,7 @@ niv_status mc_irradiance_at(const mc_scene *s, const float *x, const float *nrm,
     a.nb = s->nk[0];
     for (int c = 0; c < 3; ++c) a.nr[c] = s->nk[1 + c];
     a.nd = s->nk[4];
+    a.cull = s->d_cull;
     a.lights = s->d_lights;
     a.motion = s->d_motion;
     a.t = t;

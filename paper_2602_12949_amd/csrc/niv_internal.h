@@ -159,6 +159,7 @@ struct FbFrame {
     const int32_t *lights;
     const void *motion;       // float4 per primitive (scene variable), or null
     const void *recs;         // trace list of the static scene
+    const void *cull;         // its candidates, or null
     int32_t nk[5];            // its counts: boxes, rectangles by axis, disks
     int32_t n_prims, n_lights;
     float eps;
@@ -175,7 +176,7 @@ struct FbArgs {
 hipError_t launch_mc_fallback(const FbArgs &a, hipStream_t stream);
 void mc_scene_device_view(const struct mc_scene *s, const void **prims, const int32_t **lights,
                           int32_t *n_prims, int32_t *n_lights, float *eps, const void **motion);
-void mc_scene_trace_view(const struct mc_scene *s, const void **recs, int32_t nk[5]);
+void mc_scene_trace_view(const struct mc_scene *s, const void **recs, int32_t nk[5], const void **cull);
 
 }  // namespace niv
 

@@ -189,3 +189,63 @@ def test_argument_checks():
         sc.irradiance(x, x, 0, 3, O.MC_NEE, 1)
     E = sc.irradiance(x[:0], x[:0], 16, 3, O.MC_NEE, 1)  # empty is a no-op
     torch.cuda.synchronize()
+
+
+def _cull_scene(seed, n_boxes, disks, shift, hidden):
+    """A closed room of boxes and two lights (and disks), moved by `shift`; with `hidden`,
+    sixty rectangles inside a solid box that nothing outside can see, which take the
+    scene past the size whose rays are traced through candidate masks."""
+    from niv_synth import box_prim, rect_prim, disk_prim, PRIM_DTYPE
+    rng = np.random.default_rng(seed)
+    lo, hi = np.array((0.0, 0.0, 0.0)), np.array((9.0, 4.0, 6.0))
+    pr = []
+    for axis in range(3):
+        u, v = (axis + 1) % 3, (axis + 2) % 3
+        for side in range(2):
+            c = 0.5 * (lo + hi)
+            c[axis] = (hi if side else lo)[axis]
+            pr.append(rect_prim(axis, -1.0 if side else 1.0, c, (hi - lo)[u] / 2, (hi - lo)[v] / 2, rng.uniform(0.2, 0.8, 3)))
+    pr.append(box_prim((8.0, 0.0, 5.0), (8.9, 0.9, 5.9), (0.5, 0.5, 0.5)))          # the box that hides
+    for _ in range(n_boxes - 1):
+        s = rng.uniform(0.2, 1.2, 3)
+        p = lo + rng.uniform(0, 1, 3) * (np.array((7.9, 4.0, 6.0)) - lo - s)
+        pr.append(box_prim(p, p + s, rng.uniform(0.2, 0.8, 3)))
+    for _ in range(disks):
+        n = rng.standard_normal(3)
+        pr.append(disk_prim(rng.uniform(1, 3.5, 3), n / np.linalg.norm(n), rng.uniform(0.2, 0.6), albedo=(0.4, 0.5, 0.6)))
+    pr.append(rect_prim(1, -1.0, (3.0, 4.0 - 1e-3, 2.0), 0.5, 0.5, (0, 0, 0), (20, 20, 20)))
+    pr.append(disk_prim((6.0, 3.9, 4.0), (0.1, -1.0, 0.2), 0.4, emission=(9, 12, 15)) if disks else
+              rect_prim(1, -1.0, (6.0, 4.0 - 1e-3, 4.0), 0.5, 0.5, (0, 0, 0), (20, 20, 20)))
+    for k in range(60 if hidden else 0):
+        pr.append(rect_prim(k % 3, 1.0, (8.4 + 0.001 * k, 0.4, 5.4), 0.1, 0.1, (0.1, 0.1, 0.1)))
+    pr = np.array(pr, dtype=PRIM_DTYPE)
+    pr["p"] += np.float32(shift)
+    pr["q"][pr["kind"] == 0] += np.float32(shift)
+    return pr
+
+
+# candidate masks against the scan of every primitive, bit for bit: few and many
+# boxes (one and two words of the mask), disks as surfaces and as a light, a
+# scene away from the origin (a ray then also tests the surface it leaves),
+# origins outside the cells, on walls and inside boxes
+@pytest.mark.parametrize("n_boxes,disks,shift", [(8, 0, 0.0), (32, 0, 0.0), (45, 3, 0.0), (20, 6, 300.0), (8, 2, -40.0)])
+def test_candidate_masks_give_the_scan_bit_for_bit(n_boxes, disks, shift):
+    from paper_2602_12949_amd import McScene
+    rng = np.random.default_rng(n_boxes)
+    n = 700
+    x = rng.uniform((-1.0, -0.5, -0.5), (7.9, 4.5, 6.5), (n, 3))
+    x[: n // 4, 1] = 0.0                                     # on the floor
+    nrm = rng.standard_normal((n, 3))
+    nrm[: n // 4] = (0.0, 1.0, 0.0)
+    nrm[n // 4: n // 2: 3] = (0.0, 0.0, -1.0)                # zero components
+    xd = torch.from_numpy((x + shift).astype(np.float32)).cuda()
+    nd = torch.from_numpy(nrm.astype(np.float32)).cuda()
+    a = McScene(_cull_scene(5, n_boxes, disks, shift, False))
+    b = McScene(_cull_scene(5, n_boxes, disks, shift, True))
+    assert len(a.prims) <= 64 < len(b.prims)
+    for flags in (1, 2 | 4, 8):
+        ra = a.irradiance(xd, nd, 65, 3, flags, 77)
+        rb = b.irradiance(xd, nd, 65, 3, flags, 77)
+        for u, v in zip(ra, rb):
+            assert torch.equal(u, v), flags
+    assert (ra[0] > 0).any()
