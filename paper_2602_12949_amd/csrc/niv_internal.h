@@ -66,7 +66,7 @@ struct QueryArgs {
     uint32_t *fb_count;       // entries appended (may exceed fb_cap)
     uint32_t fb_cap;
     float loss_scale;         // training: 1/(3n)
-    // training forward only (the fused kernel instantiated with TRAIN, frame 0):
+    // FP32 training forward only (the fused kernel instantiated with TRAIN, frame 0):
     const float *extra_ps;    // per-sample scene variables [count][n_extra] or null
     const float *target;      // [count][3] irradiance targets
     const uint8_t *valid;     // [count] or null
@@ -76,8 +76,6 @@ struct QueryArgs {
     float *loss;              // device scalar, accumulates the Eq. 3 loss
     uint32_t *train_status;   // step words of the training scratch; [2] set by a non-finite dE
     float loss_eps;           // 0.01 (Eq. 3)
-    uint32_t l0_words;        // FP16 training forward: entries of grid level 0 (dense) held in
-    uint32_t l0_off;          // LDS, or 0; and the level's first entry
     int32_t xcd_order;        // tile order, see LaunchTune
     FrameArgs f[kMaxFrames];
 };

@@ -35,23 +35,23 @@ namespace niv {
 // Waves per SIMD the register allocation must allow: 4 for the FP16 query
 // of the staged grid shapes (at most 128 VGPRs; the LDS of a 512-thread workgroup
 // allows two workgroups per CU, i.e. four waves per SIMD), else no bound.
-template <int P, class S, bool TRAIN> constexpr int query_min_waves()
+template <int P, class S> constexpr int query_min_waves()
 {
-    return (P == NIV_FP16 && !TRAIN && !S::SL && S::PB == 0) ? 4 : 1;
+    return (P == NIV_FP16 && !S::SL && S::PB == 0) ? 4 : 1;
 }
 
 // PROBE (measurement only): the encoding stage alone, with the launch shape,
 // pixel order and encoding functions of the query, writing one word per
 // pixel (E[3q]) instead of running the network.
 template <int P, class S, bool WLDS, int TB, bool TRAIN, int BLOCK, bool PROBE = false>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(query_min_waves<P, S, TRAIN>())))
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(query_min_waves<P, S>())))
 void k_query(const QueryArgs a)
 {
     static_assert(!PROBE || (!TRAIN && !S::SL), "probe: staged query encoding");
     // BLOCK threads at most; small calls launch 64 or 128
     const int n_threads = BLOCK > 256 ? BLOCK : (int)blockDim.x, n_waves = n_threads / 64;
     using O = Ops<P, S>;
-    static_assert(!TRAIN || (TB == 4 && P != NIV_BF16), "training: four tiles, FP32 or FP16");
+    static_assert(!TRAIN || (TB == 4 && P == NIV_FP32), "training: four tiles, FP32 (FP16: k_train_mlp)");
     static_assert(!S::SL || WLDS, "lane slices read the level table from LDS");
     static_assert(!TRAIN || S::DIN == S::DIN_IN, "training: kernel columns are the parameter columns");
     // training saves: per 64-sample chunk, X_0 (DIN rows) then X_1..X_H (W rows), each [row][64]
@@ -97,11 +97,6 @@ void k_query(const QueryArgs a)
                     const u4 *lsrc = reinterpret_cast<const u4 *>(fmodel);
                     u4 *ldst = reinterpret_cast<u4 *>(smem + O::W_BYTES);
                     for (int k = threadIdx.x; k < kLevelBytes / 16; k += n_threads) ldst[k] = lsrc[k];
-                }
-                if constexpr (TRAIN && P == NIV_FP16) {  // grid level 0 behind the staging blocks
-                    const uint32_t *gsrc = reinterpret_cast<const uint32_t *>(fmodel + a.grid_off) + a.l0_off;
-                    uint32_t *l0 = reinterpret_cast<uint32_t *>(smem + O::W_BYTES) + n_waves * 64 * O::ROW_DW;
-                    for (uint32_t k = threadIdx.x; k < a.l0_words; k += n_threads) l0[k] = gsrc[k];
                 }
                 __syncthreads();
                 staged = fi;
@@ -344,7 +339,7 @@ void k_query(const QueryArgs a)
 
         uint32_t *row = stage + lane * O::ROW_DW;
         // the FP16 query takes its cell coordinates in FP32
-        constexpr bool F32C = (P == NIV_FP16) && !TRAIN;
+        constexpr bool F32C = P == NIV_FP16;
         // the FP32 and BF16 queries overlap the levels' gathers; the FP16
         // query and the training forward go level by level (measured faster:
         // paired dense loads, and the training kernel's registers)
@@ -402,17 +397,7 @@ void k_query(const QueryArgs a)
                 const float pf[3] = {(float)p[0], (float)p[1], (float)p[2]};
 #pragma unroll
                 for (int l = 0; l < S::L; ++l) {
-                    f2 f;
-                    if (TRAIN && P == NIV_FP16 && l == 0 && a.l0_words) {
-                        // the training forward's samples are spread over the
-                        // volume: level 0 comes from its LDS copy instead of
-                        // a gather touching a cache line per lane
-                        const uint32_t *l0 = reinterpret_cast<const uint32_t *>(smem + O::W_BYTES) +
-                                             n_waves * 64 * O::ROW_DW;
-                        f = encode_dense_lds<P>(lvs[0], p, l0);
-                    } else {
-                        f = encode_level_buf<P, F32C>(lvs[l], p, a.hash_mask, grid_rsrc, pf);
-                    }
+                    const f2 f = encode_level_buf<P, F32C>(lvs[l], p, a.hash_mask, grid_rsrc, pf);
                     if constexpr (P == NIV_FP32) {
                         row[2 * l] = f2u(f.x);
                         row[2 * l + 1] = f2u(f.y);
@@ -526,17 +511,8 @@ void k_query(const QueryArgs a)
         }
         if constexpr (TRAIN) {
             uint8_t *xs = a.x_save + chunk * CHUNK_BYTES;
-            if constexpr (P == NIV_FP32) {
 #pragma unroll
-                for (int k = 0; k < S::DIN; ++k)
-                    reinterpret_cast<uint32_t *>(xs)[k * 64 + lane] = row[k];
-            } else {
-#pragma unroll
-                for (int k = 0; k < S::DIN / 2; ++k) {
-                    reinterpret_cast<uint16_t *>(xs)[(2 * k) * 64 + lane] = (uint16_t)(row[k] & 0xffffu);
-                    reinterpret_cast<uint16_t *>(xs)[(2 * k + 1) * 64 + lane] = (uint16_t)(row[k] >> 16);
-                }
-            }
+            for (int k = 0; k < S::DIN; ++k) reinterpret_cast<uint32_t *>(xs)[k * 64 + lane] = row[k];
         }
         if constexpr (PROBE) {
             uint32_t xo = 0u;
@@ -717,48 +693,6 @@ void k_query(const QueryArgs a)
                                                     bh[O::NS - 1][t][2 * ob + 1]);
                             }
                         }
-                    if constexpr (TRAIN) {
-                        // the layer's input, [neuron][64 samples], through this
-                        // wave's staging block (free once layer 0 has read it)
-                        // in halves of 32 neurons: 2-byte LDS writes, then
-                        // coalesced 16-byte stores
-                        uint8_t *xs = a.x_save + chunk * CHUNK_BYTES + (S::DIN + (layer - 1) * S::W) * 64 * 2;
-                        constexpr int RS = 68;   // halves per staged row (64 samples + padding)
-                        static_assert(32 * RS * 2 <= 64 * O::ROW_DW * 4, "half a layer fits the staging block");
-                        uint16_t *tb16 = reinterpret_cast<uint16_t *>(stage);
-                        uint32_t mk[S::W / 32];
-#pragma unroll
-                        for (int d = 0; d < S::W / 32; ++d) mk[d] = 0u;
-#pragma unroll
-                        for (int hf = 0; hf < 2; ++hf) {
-                            wave_lds_fence();
-#pragma unroll
-                            for (int t = 0; t < TB; ++t)
-#pragma unroll
-                                for (int ob = 2 * hf; ob < 2 * hf + 2; ++ob)
-#pragma unroll
-                                    for (int r = 0; r < 4; ++r) {
-                                        const uint32_t w2 = bh[0][t][2 * ob + (r >> 1)];
-                                        const uint16_t hv = (uint16_t)((r & 1) ? (w2 >> 16) : (w2 & 0xffffu));
-                                        tb16[(16 * (ob - 2 * hf) + 4 * g + r) * RS + 16 * t + j] = hv;
-                                        const int bit = (t * S::NOB + ob) * 4 + r;
-                                        mk[bit >> 5] |= (hv != 0 ? 1u : 0u) << (bit & 31);
-                                    }
-                            wave_lds_fence();
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                const int ci = lane + 64 * i, row = ci >> 3, c = ci & 7;
-                                const u2 lo = *reinterpret_cast<const u2 *>(tb16 + row * RS + 8 * c);
-                                const u2 hi = *reinterpret_cast<const u2 *>(tb16 + row * RS + 8 * c + 4);
-                                *reinterpret_cast<u4 *>(xs + ((32 * hf + row) * 64 + 8 * c) * 2) =
-                                    (u4){lo.x, lo.y, hi.x, hi.y};
-                            }
-                        }
-                        wave_lds_fence();   // the staging block is written again by the next tile
-#pragma unroll
-                        for (int d = 0; d < S::W / 32; ++d)
-                            a.mask_save[((chunk * S::H + (layer - 1)) * (S::W / 32) + d) * 64 + lane] = mk[d];
-                    }
                     // a block row of operands: HF full-depth, then HH half-depth
                     if (last) {
 #pragma unroll

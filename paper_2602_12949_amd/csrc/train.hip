@@ -3,24 +3,27 @@
 // encoding gradient into the hash grid, and Adam.
 //
 // A step runs these stages on the caller's stream:
-//   1. the fused query kernel in training mode: encodes each sample, runs
-//      the MLP, saves every layer's input (per 64-sample chunk, row-major
-//      [neuron][sample], the layout the weight-gradient products read) and
-//      the ReLU masks, and writes d loss / dE (Eq. 3, stop-gradient
-//      denominator) and the loss;
-//   2. k_train_bwd: per chunk, the weight gradients dW_k = G_{k+1} X_k^T on
-//      MFMA (the gradient is transposed through LDS), the input gradients
-//      W_k^T G_{k+1} on MFMA with pre-permuted transposed weights so that
-//      they come out in the same lane layout as the forward activations;
-//      each wave keeps its weight gradient in the matrix-core accumulators
-//      over its chunks, a workgroup's four waves add theirs in LDS and
-//      write one row, and k_dw_sum adds the rows; the gradient of each
-//      sample's grid features is written out level-major per chunk;
+//   1. FP16: k_train_encode writes the samples' input vectors, and
+//      k_train_mlp takes 64 samples at a time forward, through the loss
+//      (Eq. 3, stop-gradient denominator) and backward without leaving
+//      registers and LDS: the weight gradients dW_k = G_{k+1} X_k^T and the
+//      input gradients W_k^T G_{k+1}, all on MFMA;
+//      FP32 (its activations do not fit a wave's registers): the fused query
+//      kernel in training mode saves every layer's input (per 64-sample
+//      chunk, [neuron][sample]) and the ReLU masks and writes d loss / dE,
+//      and k_train_bwd walks back through them (the gradient is transposed
+//      through LDS for dW);
+//   2. in both, pre-permuted transposed weights make the input gradients come
+//      out in the lane layout of the forward activations; each wave keeps
+//      its weight gradient in the matrix-core accumulators over its chunks,
+//      a workgroup's four waves add theirs in LDS and write one row, and
+//      k_dw_sum adds the rows; the gradient of each sample's grid features
+//      is written out level-major per chunk;
 //   3. the scatter of those feature gradients to the 8 corners of every
 //      level, without global atomics (device-scope atomics execute at the
 //      memory side of this part, ~22 G/s): the contributions are counted
 //      per bin of 4096 grid entries and workgroup (k_grid_count, on a
-//      second stream beside the forward: it needs only the batch), the
+//      second stream beside stage 1: it needs only the batch), the
 //      counts are scanned (k_grid_scan_bins; the bins' totals at the start
 //      of the write pass), the contributions are written bin by bin
 //      (k_grid_write), and one or more workgroups per bin sum them in LDS
@@ -37,6 +40,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 
 #include "niv_internal.h"
@@ -47,7 +51,6 @@
 namespace niv {
 
 constexpr int kMaxMats = 12;   // weight matrices of a model (n_hidden + 1) niv_init_params takes
-constexpr int kL0Words = 5120;  // LDS copy of grid level 0 in the FP16 training forward (20 KB)
 
 // ---------------------------------------------------------------- layouts
 template <int P, class S> struct Bwd {
@@ -71,6 +74,11 @@ template <int P, class S> struct Bwd {
     static constexpr int NFP = 2 * S::L + 2;                  // padded row of the grid-feature gradient
     static constexpr int DX_BYTES = 64 * NFP * 4;              // grid-feature gradient, [64][2L + 2]
     static constexpr int WB_BYTES = (GB_BYTES > DX_BYTES ? GB_BYTES : DX_BYTES) + 3 * 64 * 4;
+    // k_train_mlp: both operand blocks, then the waves' (feature gradient, dE)
+    static constexpr int MLP_W_BYTES = Ops<P, S>::W_BYTES + BYTES;
+    static constexpr int MLP_WAVE_BYTES = DX_BYTES + 3 * 64 * 4;
+    static constexpr int MLP_LDS = MLP_W_BYTES + 4 * MLP_WAVE_BYTES;
+    static_assert(MLP_LDS >= NMLP * 4 || F32, "the workgroup's weight gradient fits over them");
     // LDS of a workgroup: four waves' blocks, reused at the end for the
     // workgroup's weight gradient
     static constexpr int LDS_BYTES = 4 * WB_BYTES > NMLP * 4 ? 4 * WB_BYTES : NMLP * 4;
@@ -153,17 +161,13 @@ struct BwdArgs {
     const uint32_t *mask_save;
     const float *dE;           // [n][3], without the 1/(3n) factor
     const float *x;            // [n][3] sample positions
-    const uint8_t *model;      // prepared model (level table first)
-    float *grads;              // [n_params]
     float *dw_part;            // [workgroup][weights] each workgroup's weight gradient
     float *dx0;                // [chunk][L][64] float pairs: gradient of each sample's grid features
     uint8_t *sflag;            // [n] 1: the sample's features scatter into the grid
     uint32_t *vmax;            // step word [0]: largest |feature gradient| x loss_scale of a
                                // scattering sample (float bits; bounds every contribution)
-    int64_t n, n_grid;
+    int64_t n;
     float loss_scale;
-    uint32_t hash_mask;
-    double lo[3], hi[3];
 };
 
 template <int P> struct Mm;
@@ -174,9 +178,84 @@ template <> struct Mm<NIV_FP16> {
     }
 };
 
+// The step's bound on the grid contributions (|w g| <= |g|, weights <= 1):
+// the scale of the fixed-point sums and of 16-bit contribution records.
+// gmax: largest |feature gradient| of the lane's scattering samples.
+__device__ inline void grad_bound(float gmax, float loss_scale, uint32_t *vmax, int lane)
+{
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) gmax = fmaxf(gmax, __shfl_xor(gmax, off));
+    const float cmax = gmax * loss_scale;
+    if (lane == 0 && cmax == cmax && cmax > 0.0f) atomicMax(vmax, f2u(cmax));
+}
+
+// The workgroup's weight gradient: the four waves add their tiles into one
+// LDS copy (over whatever it held), wave after wave, and it goes out as one
+// row; k_dw_sum adds the rows (no atomics, a fixed summation order).  Tile
+// element r of lane (g, j) is row 16 ob + 4 g + r, column 16 ib + j of the
+// layer's matrix.
 template <int P, class S>
+__device__ __forceinline__ void store_weight_gradient(const f4 (&dwacc)[Bwd<P, S>::N_TILES], uint8_t *smem, float *dw_part,
+                                                      int wave, int g, int j)
+{
+    using B = Bwd<P, S>;
+    __syncthreads();   // every wave is done with its block
+    float *red = reinterpret_cast<float *>(smem);
+    for (int k = threadIdx.x; k < B::NMLP; k += 256) red[k] = 0.0f;
+    __syncthreads();
+    for (int w = 0; w < 4; ++w) {
+        if (wave == w) {
+            {
+                const int woff = S::W * S::DIN + (S::H - 1) * S::W * S::W;   // output layer [3][W]
+#pragma unroll
+                for (int nb = 0; nb < S::W / 16; ++nb)
+                    if (g == 0) {
+                        red[woff + 0 * S::W + 16 * nb + j] += dwacc[nb].x;
+                        red[woff + 1 * S::W + 16 * nb + j] += dwacc[nb].y;
+                        red[woff + 2 * S::W + 16 * nb + j] += dwacc[nb].z;
+                    }
+            }
+#pragma unroll
+            for (int k = S::H - 1; k >= 0; --k) {
+                const int dk = (k == 0) ? S::DIN : S::W;
+                const int woff = (k == 0) ? 0 : S::W * S::DIN + (k - 1) * S::W * S::W;
+                const int tb = B::tile_base(k);
+#pragma unroll
+                for (int ob = 0; ob < B::NOB; ++ob)
+#pragma unroll
+                    for (int ib = 0; ib < (S::DIN > S::W ? S::DIN : S::W) / 16; ++ib) {
+                        if (ib * 16 >= dk) break;
+                        const f4 v = dwacc[tb + ob * (dk / 16) + ib];
+                        float *dst = red + woff + (16 * ob + 4 * g) * dk + 16 * ib + j;
+                        dst[0] += v.x;
+                        dst[dk] += v.y;
+                        dst[2 * dk] += v.z;
+                        dst[3 * dk] += v.w;
+                    }
+            }
+        }
+        __syncthreads();
+    }
+    float *row = dw_part + (int64_t)blockIdx.x * B::NMLP;
+    for (int k = threadIdx.x; k < B::NMLP; k += 256) row[k] = red[k];
+}
+
+// Two halves at a time: 1 where a half is not +0 (after a ReLU there is no -0),
+// and a half kept (m = 1) or zeroed (m = 0).
+typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+__device__ inline uint32_t nonzero2(uint32_t w)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(us2, w), (us2){1, 1}));
+}
+__device__ inline uint32_t keep2(uint32_t w, uint32_t m)
+{
+    return __builtin_bit_cast(uint32_t, (us2)(__builtin_bit_cast(us2, w) * __builtin_bit_cast(us2, m)));
+}
+
+template <class S>
 __global__ __launch_bounds__(256) void k_train_bwd(const BwdArgs a)
 {
+    constexpr int P = NIV_FP32;
     using B = Bwd<P, S>;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -209,41 +288,21 @@ __global__ __launch_bounds__(256) void k_train_bwd(const BwdArgs a)
         // (the X_H operands are loaded together first: one memory latency)
         {
             const int xrow = S::DIN + (S::H - 1) * S::W;
-            if constexpr (B::F32) {
-                const float *xf = reinterpret_cast<const float *>(xs);
-                float xv[S::W / 16][16];
+            const float *xf = reinterpret_cast<const float *>(xs);
+            float xv[S::W / 16][16];
 #pragma unroll
-                for (int nb = 0; nb < S::W / 16; ++nb)
+            for (int nb = 0; nb < S::W / 16; ++nb)
 #pragma unroll
-                    for (int s = 0; s < 16; ++s) xv[nb][s] = xf[(xrow + 16 * nb + j) * 64 + 4 * s + g];
+                for (int s = 0; s < 16; ++s) xv[nb][s] = xf[(xrow + 16 * nb + j) * 64 + 4 * s + g];
 #pragma unroll
-                for (int nb = 0; nb < S::W / 16; ++nb) {
-                    f4 acc = dwacc[nb];
+            for (int nb = 0; nb < S::W / 16; ++nb) {
+                f4 acc = dwacc[nb];
 #pragma unroll
-                    for (int s = 0; s < 16; ++s) {
-                        const float av = j < 3 ? debuf[j * 64 + 4 * s + g] : 0.f;
-                        acc = Prec<NIV_FP32>::mma1(av, xv[nb][s], acc);
-                    }
-                    dwacc[nb] = acc;
+                for (int s = 0; s < 16; ++s) {
+                    const float av = j < 3 ? debuf[j * 64 + 4 * s + g] : 0.f;
+                    acc = Prec<NIV_FP32>::mma1(av, xv[nb][s], acc);
                 }
-            } else {
-                u4 xv[S::W / 16][2];
-#pragma unroll
-                for (int nb = 0; nb < S::W / 16; ++nb)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-                        xv[nb][h] = *reinterpret_cast<const u4 *>(
-                            xs + ((int64_t)(xrow + 16 * nb + j) * 64 + 32 * h + 8 * g) * 2);
-                u4 av[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
-                if (j < 3) {
-                    av[0] = Mm<P>::h8(debuf + j * 64 + 8 * g);
-                    av[1] = Mm<P>::h8(debuf + j * 64 + 32 + 8 * g);
-                }
-#pragma unroll
-                for (int nb = 0; nb < S::W / 16; ++nb) {
-                    dwacc[nb] = Prec<P>::mma(av[0], xv[nb][0], dwacc[nb]);
-                    dwacc[nb] = Prec<P>::mma(av[1], xv[nb][1], dwacc[nb]);
-                }
+                dwacc[nb] = acc;
             }
         }
         // ---- gradient w.r.t. x_H = W_H^T dE, lane layout of the forward
@@ -253,19 +312,9 @@ __global__ __launch_bounds__(256) void k_train_bwd(const BwdArgs a)
 #pragma unroll
             for (int ib = 0; ib < B::NIB; ++ib) {
                 const f4 z = {0.f, 0.f, 0.f, 0.f};
-                if constexpr (B::F32) {
-                    const float av = reinterpret_cast<const float *>(bw + ib * B::OUT_OP)[lane];
-                    const float bv = g < 3 ? debuf[g * 64 + 16 * t + j] : 0.f;
-                    G[t][ib] = Prec<NIV_FP32>::mma1(av, bv, z);
-                } else {
-                    const u2 av = reinterpret_cast<const u2 *>(bw + ib * B::OUT_OP)[lane];
-                    u2 bv = {0u, 0u};
-                    if (g == 0) {
-                        bv.x = Prec<P>::pack(debuf[16 * t + j], debuf[64 + 16 * t + j]);
-                        bv.y = Prec<P>::pack(debuf[128 + 16 * t + j], 0.f);
-                    }
-                    G[t][ib] = Prec<P>::mma_half(av, bv, z);
-                }
+                const float av = reinterpret_cast<const float *>(bw + ib * B::OUT_OP)[lane];
+                const float bv = g < 3 ? debuf[g * 64 + 16 * t + j] : 0.f;
+                G[t][ib] = Prec<NIV_FP32>::mma1(av, bv, z);
             }
         // ---- hidden layers k = H-1 .. 0
 #pragma unroll
@@ -286,29 +335,16 @@ __global__ __launch_bounds__(256) void k_train_bwd(const BwdArgs a)
                     if (!((mk[(b0 + 3) >> 5] >> ((b0 + 3) & 31)) & 1u)) G[t][ob].w = 0.f;
                 }
             // transpose G through LDS: [neuron][64 samples]
-            if constexpr (B::F32) {
-                float *gb = reinterpret_cast<float *>(wbuf);
+            float *gb = reinterpret_cast<float *>(wbuf);
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
+            for (int t = 0; t < 4; ++t)
 #pragma unroll
-                    for (int ob = 0; ob < B::NOB; ++ob) {
-                        gb[(16 * ob + 4 * g + 0) * 64 + 16 * t + j] = G[t][ob].x;
-                        gb[(16 * ob + 4 * g + 1) * 64 + 16 * t + j] = G[t][ob].y;
-                        gb[(16 * ob + 4 * g + 2) * 64 + 16 * t + j] = G[t][ob].z;
-                        gb[(16 * ob + 4 * g + 3) * 64 + 16 * t + j] = G[t][ob].w;
-                    }
-            } else {
-                _Float16 *gb = reinterpret_cast<_Float16 *>(wbuf);
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int ob = 0; ob < B::NOB; ++ob) {
-                        gb[(16 * ob + 4 * g + 0) * 64 + 16 * t + j] = (_Float16)G[t][ob].x;
-                        gb[(16 * ob + 4 * g + 1) * 64 + 16 * t + j] = (_Float16)G[t][ob].y;
-                        gb[(16 * ob + 4 * g + 2) * 64 + 16 * t + j] = (_Float16)G[t][ob].z;
-                        gb[(16 * ob + 4 * g + 3) * 64 + 16 * t + j] = (_Float16)G[t][ob].w;
-                    }
-            }
+                for (int ob = 0; ob < B::NOB; ++ob) {
+                    gb[(16 * ob + 4 * g + 0) * 64 + 16 * t + j] = G[t][ob].x;
+                    gb[(16 * ob + 4 * g + 1) * 64 + 16 * t + j] = G[t][ob].y;
+                    gb[(16 * ob + 4 * g + 2) * 64 + 16 * t + j] = G[t][ob].z;
+                    gb[(16 * ob + 4 * g + 3) * 64 + 16 * t + j] = G[t][ob].w;
+                }
             wave_lds_fence();
             // dW_k += G X_k^T over the chunk's 64 samples; the X_k operands do
             // not depend on the output block and are loaded together first
@@ -316,92 +352,42 @@ __global__ __launch_bounds__(256) void k_train_bwd(const BwdArgs a)
             const int dk = (k == 0) ? S::DIN : S::W;
             const int xrow = (k == 0) ? 0 : S::DIN + (k - 1) * S::W;
             const int tb = B::tile_base(k);   // this layer's tiles: ob * (dk / 16) + ib
-            if constexpr (B::F32) {
-                const float *gb = reinterpret_cast<const float *>(wbuf);
-                const float *xf = reinterpret_cast<const float *>(xs);
-                float xv[DK_MAX / 16][16];
+            const float *xf = reinterpret_cast<const float *>(xs);
+            float xv[DK_MAX / 16][16];
 #pragma unroll
-                for (int ib = 0; ib < DK_MAX / 16; ++ib)
+            for (int ib = 0; ib < DK_MAX / 16; ++ib)
+#pragma unroll
+                for (int s = 0; s < 16; ++s)
+                    xv[ib][s] = ib * 16 < dk ? xf[(int64_t)(xrow + 16 * ib + j) * 64 + 4 * s + g] : 0.f;
+#pragma unroll
+            for (int ob = 0; ob < B::NOB; ++ob)
+#pragma unroll
+                for (int ib = 0; ib < DK_MAX / 16; ++ib) {
+                    if (ib * 16 >= dk) break;
+                    f4 acc = dwacc[tb + ob * (dk / 16) + ib];
 #pragma unroll
                     for (int s = 0; s < 16; ++s)
-                        xv[ib][s] = ib * 16 < dk ? xf[(int64_t)(xrow + 16 * ib + j) * 64 + 4 * s + g] : 0.f;
-#pragma unroll
-                for (int ob = 0; ob < B::NOB; ++ob)
-#pragma unroll
-                    for (int ib = 0; ib < DK_MAX / 16; ++ib) {
-                        if (ib * 16 >= dk) break;
-                        f4 acc = dwacc[tb + ob * (dk / 16) + ib];
-#pragma unroll
-                        for (int s = 0; s < 16; ++s)
-                            acc = Prec<NIV_FP32>::mma1(gb[(16 * ob + j) * 64 + 4 * s + g], xv[ib][s], acc);
-                        dwacc[tb + ob * (dk / 16) + ib] = acc;
-                    }
-            } else {
-                u4 xv[DK_MAX / 16][2];
-#pragma unroll
-                for (int ib = 0; ib < DK_MAX / 16; ++ib)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-                        xv[ib][h] = ib * 16 < dk ? *reinterpret_cast<const u4 *>(
-                                        xs + ((int64_t)(xrow + 16 * ib + j) * 64 + 32 * h + 8 * g) * 2)
-                                                 : (u4){0u, 0u, 0u, 0u};
-#pragma unroll
-                for (int ob = 0; ob < B::NOB; ++ob) {
-                    const u4 av0 = *reinterpret_cast<const u4 *>(wbuf + ((16 * ob + j) * 64 + 8 * g) * 2);
-                    const u4 av1 = *reinterpret_cast<const u4 *>(wbuf + ((16 * ob + j) * 64 + 32 + 8 * g) * 2);
-#pragma unroll
-                    for (int ib = 0; ib < DK_MAX / 16; ++ib) {
-                        if (ib * 16 >= dk) break;
-                        f4 &acc = dwacc[tb + ob * (dk / 16) + ib];
-                        acc = Prec<P>::mma(av0, xv[ib][0], acc);
-                        acc = Prec<P>::mma(av1, xv[ib][1], acc);
-                    }
+                        acc = Prec<NIV_FP32>::mma1(gb[(16 * ob + j) * 64 + 4 * s + g], xv[ib][s], acc);
+                    dwacc[tb + ob * (dk / 16) + ib] = acc;
                 }
-            }
             // d loss / d x_k = W_k^T G (grid rows only for k = 0)
             const int nib = (k == 0) ? B::GIB : B::NIB;
             const uint8_t *bk = (k == 0) ? bw + B::OUT_BYTES + (S::H - 1) * B::HID_BYTES
                                          : bw + B::OUT_BYTES + (k - 1) * B::HID_BYTES;
             f4 Gn[4][B::NOB];
-            if constexpr (B::F32) {
 #pragma unroll
-                for (int ib = 0; ib < B::NIB; ++ib) {
-                    if (ib >= nib) break;
+            for (int ib = 0; ib < B::NIB; ++ib) {
+                if (ib >= nib) break;
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) Gn[t][ib] = (f4){0.f, 0.f, 0.f, 0.f};
+                for (int t = 0; t < 4; ++t) Gn[t][ib] = (f4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int c = 0; c < B::HOPS; ++c) {
-                        const float av = reinterpret_cast<const float *>(bk + (ib * B::HOPS + c) * B::OPB)[lane];
+                for (int c = 0; c < B::HOPS; ++c) {
+                    const float av = reinterpret_cast<const float *>(bk + (ib * B::HOPS + c) * B::OPB)[lane];
 #pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            const f4 gv = G[t][c / 4];
-                            const float bv = (c % 4 == 0) ? gv.x : (c % 4 == 1) ? gv.y : (c % 4 == 2) ? gv.z : gv.w;
-                            Gn[t][ib] = Prec<NIV_FP32>::mma1(av, bv, Gn[t][ib]);
-                        }
-                    }
-                }
-            } else {
-                uint32_t bg[4][S::W / 8];
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int ob = 0; ob < B::NOB; ++ob) {
-                        bg[t][2 * ob] = Prec<P>::pack(G[t][ob].x, G[t][ob].y);
-                        bg[t][2 * ob + 1] = Prec<P>::pack(G[t][ob].z, G[t][ob].w);
-                    }
-#pragma unroll
-                for (int ib = 0; ib < B::NIB; ++ib) {
-                    if (ib >= nib) break;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) Gn[t][ib] = (f4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int kb = 0; kb < B::HOPS; ++kb) {
-                        const u4 av = reinterpret_cast<const u4 *>(bk + (ib * B::HOPS + kb) * B::OPB)[lane];
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            const u4 bv = {bg[t][4 * kb], bg[t][4 * kb + 1], bg[t][4 * kb + 2], bg[t][4 * kb + 3]};
-                            Gn[t][ib] = Prec<P>::mma(av, bv, Gn[t][ib]);
-                        }
+                    for (int t = 0; t < 4; ++t) {
+                        const f4 gv = G[t][c / 4];
+                        const float bv = (c % 4 == 0) ? gv.x : (c % 4 == 1) ? gv.y : (c % 4 == 2) ? gv.z : gv.w;
+                        Gn[t][ib] = Prec<NIV_FP32>::mma1(av, bv, Gn[t][ib]);
                     }
                 }
             }
@@ -446,55 +432,458 @@ __global__ __launch_bounds__(256) void k_train_bwd(const BwdArgs a)
             }
         }
     }
-    // the step's bound on the grid contributions (|w g| <= |g|, weights <= 1):
-    // the scale of the fixed-point sums and of 16-bit contribution records
+    grad_bound(gmax, a.loss_scale, a.vmax, lane);
+    store_weight_gradient<P, S>(dwacc, smem, a.dw_part, wave, g, j);
+}
+
+// ---------------------------------------------------------------- FP16: encoding
+// The input vectors of a batch.  A sample's 128 latents lie at random in a
+// 7 MB table, so the pass is bound by the rate of cache lines from L2.  The
+// levels are dealt to the XCDs, two each, so that a 4 MB L2 holds its levels
+// whole: 83 us at 2^18 samples of the room network, against 102 us with
+// every XCD taking every level, one pair after the other.  Encoding inside
+// the forward's kernel (two waves per SIMD beside its weights) took 135 us
+// for both.  The count pass beside it costs nothing (83 us without it).
+// Input dword k (columns 2k, 2k + 1) of sample q of a chunk goes to
+// x_pair[chunk][k][q], and column c to x_row[chunk][c][q]: the forward reads
+// the pairs, the weight gradient the rows.
+struct EncodeArgs {
+    const float *x, *nrm, *extra;   // [n][3], [n][3], [n][n_extra]
+    const uint8_t *valid;           // [n] or null
+    const uint8_t *model;           // prepared model (level table first)
+    uint64_t grid_off;
+    uint32_t grid_bytes, hash_mask;
+    uint32_t *x_pair;
+    uint16_t *x_row;
+    int64_t n;
+    double lo[3], hi[3];
+};
+
+constexpr int kEncWaves = 4;
+
+template <class S>
+__global__ __launch_bounds__(64 * kEncWaves) void k_train_encode(const EncodeArgs a)
+{
+    typedef const __attribute__((address_space(4))) LevelConst *ConstLevels;
+    constexpr int P = NIV_FP16;
+    constexpr int PER = (S::L + kXcds - 1) / kXcds;   // levels of an XCD
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int xcd = blockIdx.x % kXcds;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(a.model + a.grid_off), (short)0, (int)a.grid_bytes, 0x00020000);
+    ConstLevels lvs = (ConstLevels)a.model;
+    static_assert(S::GF / 2 + 8 + 8 * S::NEX == S::DIN / 2, "grid, normal and scene columns fill the rows");
+    static_assert(S::H * S::W >= S::DIN, "both copies of the inputs fit the chunk's saved rows");
+    const int64_t chunk = (int64_t)(blockIdx.x / kXcds) * kEncWaves + wave;
+    if (chunk * 64 >= a.n) return;
+    const int64_t q = chunk * 64 + lane;
+    const bool live = q < a.n, on = live && (!a.valid || a.valid[q] != 0);
+    float v[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (on) {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) gmax = fmaxf(gmax, __shfl_xor(gmax, off));
-    const float cmax = gmax * a.loss_scale;
-    if (lane == 0 && cmax == cmax && cmax > 0.0f) atomicMax(a.vmax, f2u(cmax));
-    // the workgroup's weight gradient: the four waves add their tiles into
-    // one LDS copy, wave after wave, and it goes out as one row; k_dw_sum adds
-    // the rows (no atomics, a fixed summation order).  Tile element r of lane
-    // (g, j) is row 16 ob + 4 g + r, column 16 ib + j of the layer's matrix.
-    __syncthreads();   // every wave is done with its block
-    float *red = reinterpret_cast<float *>(smem);
-    for (int k = threadIdx.x; k < B::NMLP; k += 256) red[k] = 0.0f;
+        for (int c = 0; c < 3; ++c) { v[c] = a.x[3 * q + c]; v[3 + c] = a.nrm[3 * q + c]; }
+    }
+    // the samples that the network computes, as in the query
+    bool work = on;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) work = work && __builtin_isfinite(v[c]);
+    float te[S::NEX > 0 ? S::NEX : 1];
+#pragma unroll
+    for (int e = 0; e < S::NEX; ++e) {
+        te[e] = live ? a.extra[q * S::NEX + e] : 0.0f;
+        work = work && __builtin_isfinite(te[e]);
+    }
+    const float nm = fmaxf(fabsf(v[3]), fmaxf(fabsf(v[4]), fabsf(v[5])));
+    work = work && nm > 0.0f;
+    uint32_t *pair = a.x_pair + chunk * (S::DIN / 2) * 64 + lane;
+    uint16_t *row = a.x_row + chunk * S::DIN * 64 + lane;
+    auto put = [&](int k, uint32_t w) {   // no bias anywhere: a sample without work feeds zeros
+        w = work ? w : 0u;
+        pair[k * 64] = w;
+        row[(2 * k) * 64] = (uint16_t)w;
+        row[(2 * k + 1) * 64] = (uint16_t)(w >> 16);
+    };
+    double p[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const double x = work ? (double)v[c] : a.lo[c];
+        p[c] = x < a.lo[c] ? a.lo[c] : (x > a.hi[c] ? a.hi[c] : x);
+    }
+    // fine and coarse levels in pairs
+    LevelFetch<P> f[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int l = i == 0 ? xcd : S::L - 1 - xcd;
+        if (l < S::L) level_issue<P, false>(lvs[l], p, a.hash_mask, rsrc, nullptr, f[i]);
+    }
+    if (chunk % kXcds == xcd) {   // the columns behind the grid's, by one XCD
+        const float ns = nm > 0.0f ? 1.0f / nm : 0.0f;
+        const float nx = v[3] * ns, ny = v[4] * ns, nz = v[5] * ns;
+        const float rn = __builtin_amdgcn_rsqf(nx * nx + ny * ny + nz * nz);
+        float sh[16];
+        sh16(nx * rn, ny * rn, nz * rn, sh);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) put(S::GF / 2 + k, Prec<P>::pack(sh[2 * k], sh[2 * k + 1]));
+#pragma unroll
+        for (int e = 0; e < S::NEX; ++e)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float t = te[e] * (float)(1 << k);
+                put(S::GF / 2 + 8 + 8 * e + k, Prec<P>::pack(sinpif(t), cospif(t)));
+            }
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int l = i == 0 ? xcd : S::L - 1 - xcd;
+        if (l >= S::L) continue;
+        const f2 r = level_blend<P>(f[i]);
+        put(l, Prec<P>::pack(r.x, r.y));
+    }
+}
+
+// ---------------------------------------------------------------- FP16: network
+struct MlpArgs {
+    const uint8_t *fwd, *bwd;       // operand blocks of the forward (prepared model) and backward
+    const uint32_t *x_pair;         // the batch's inputs, see k_train_encode
+    const uint16_t *x_row;
+    const float *x, *nrm, *extra, *target;
+    const uint8_t *valid;
+    float *dw_part;                 // [workgroup][weights]
+    float *dx0;                     // [chunk][L][64] float pairs
+    uint8_t *sflag;                 // [n] 1: the sample's features scatter into the grid
+    uint32_t *status;               // step words: [0] bound on the contributions, [2] not finite
+    float *loss;
+    int64_t n;
+    float loss_scale, loss_eps;
+};
+
+// Forward, loss and backward of 64 samples at a time, one wave per SIMD (the
+// weight gradient of all its chunks stays in the matrix cores' accumulators,
+// ~200 registers).  Every product is formed twice, with its operands swapped:
+// W X leaves a lane with rows (neurons) of one sample, which is the next
+// layer's operand; X^T W^T leaves it with rows (samples) of one neuron, which
+// is the operand of the weight gradients dW = G X^T.  Matrix products are
+// cheap here (the pass issues a tenth of the matrix cores' rate); what they
+// replace is each layer's input written to memory by a forward kernel, read
+// back by a backward one, and gradients transposed through LDS, two bytes an
+// instruction.  Sample of column j of tile t: sample_of(t, j), chosen so that
+// the contraction of a weight gradient runs over the samples in their order.
+// 2^18 samples of the room network: forward 135 us (with its encoding) and
+// backward 84 us before, encoding 83 us and this kernel 73 us now.  It is
+// bound by latency (one wave per SIMD: 13 us a chunk, 22 us for the weights
+// and the final reduction); the blocks of a layer are kept apart for the
+// scheduler, which otherwise takes 83 us, and the layers' inputs are packed
+// where they come out, without which 100 registers go to scratch (125 us).
+__device__ constexpr int sample_of(int t, int j) { return 32 * (t >> 1) + 8 * (j >> 2) + 4 * (t & 1) + (j & 3); }
+
+template <class S>
+__global__ __launch_bounds__(256) void k_train_mlp(const MlpArgs a)
+{
+    constexpr int P = NIV_FP16;
+    using O = Ops<P, S>;
+    using B = Bwd<P, S>;
+    static_assert(S::W == 64, "two operands per block row");
+    constexpr int NB = S::W / 16, KB = S::W / 32, IB = S::DIN / 16;
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int g = lane >> 4, j = lane & 15;
+    uint8_t *fw = smem, *bw = smem + O::W_BYTES;
+    uint8_t *wbuf = smem + B::MLP_W_BYTES + wave * B::MLP_WAVE_BYTES;
+    float *debuf = reinterpret_cast<float *>(wbuf + B::DX_BYTES);
+    for (int k = threadIdx.x; k < O::W_BYTES / 16; k += 256)
+        reinterpret_cast<u4 *>(fw)[k] = reinterpret_cast<const u4 *>(a.fwd)[k];
+    for (int k = threadIdx.x; k < B::BYTES / 16; k += 256)
+        reinterpret_cast<u4 *>(bw)[k] = reinterpret_cast<const u4 *>(a.bwd)[k];
     __syncthreads();
-    for (int w = 0; w < 4; ++w) {
-        if (wave == w) {
-            {
-                const int woff = S::W * S::DIN + (S::H - 1) * S::W * S::W;   // output layer [3][W]
+    f4 dwacc[B::N_TILES];
 #pragma unroll
-                for (int nb = 0; nb < S::W / 16; ++nb)
-                    if (g == 0) {
-                        red[woff + 0 * S::W + 16 * nb + j] += dwacc[nb].x;
-                        red[woff + 1 * S::W + 16 * nb + j] += dwacc[nb].y;
-                        red[woff + 2 * S::W + 16 * nb + j] += dwacc[nb].z;
+    for (int t = 0; t < B::N_TILES; ++t) dwacc[t] = (f4){0.f, 0.f, 0.f, 0.f};
+    const f4 z = {0.f, 0.f, 0.f, 0.f};
+    const int64_t n_chunks = (a.n + 63) / 64;
+    const int64_t n_waves = (int64_t)gridDim.x * 4;
+    float gmax = 0.0f, lsum = 0.0f;
+    bool bad = false;
+    for (int64_t chunk = (int64_t)blockIdx.x * 4 + wave; chunk < n_chunks; chunk += n_waves) {
+        const int64_t q = chunk * 64 + lane;
+        const bool live = q < a.n;
+        // ---- this lane's sample: does it count, its target
+        bool work = live && (!a.valid || a.valid[q] != 0), pos_ok = live;
+        float y[3] = {0.f, 0.f, 0.f};
+        if (live) {
+            float nm = 0.0f;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const float xv = a.x[3 * q + c], nv = a.nrm[3 * q + c];
+                pos_ok = pos_ok && __builtin_isfinite(xv);
+                work = work && __builtin_isfinite(nv);
+                nm = fmaxf(nm, fabsf(nv));
+                y[c] = a.target[3 * q + c];
+            }
+            work = work && pos_ok && nm > 0.0f;
+#pragma unroll
+            for (int e = 0; e < S::NEX; ++e) work = work && __builtin_isfinite(a.extra[q * S::NEX + e]);
+        }
+        // ---- forward
+        uint32_t b0[4][O::LANE_DW];   // layer 0's operand
+        {
+            const uint32_t *xp = a.x_pair + (chunk * (S::DIN / 2) + O::LANE_DW * g) * 64;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int k = 0; k < O::LANE_DW; ++k) b0[t][k] = xp[k * 64 + sample_of(t, j)];
+        }
+        u4 xt[S::H][NB][2];           // X_1 .. X_H as operands of the weight gradients
+        uint32_t mk[S::H][2];         // their ReLU masks in the lane layout of the forward, two bits per dword
+        uint32_t bh[4][S::W / 8];
+#pragma unroll
+        for (int k = 0; k < S::H; ++k) {
+            uint32_t bn[4][S::W / 8];
+            const uint8_t *lw = k == 0 ? fw : fw + O::L0_BYTES + (k - 1) * O::HID_BYTES;
+#pragma unroll
+            for (int d = 0; d < 2; ++d) mk[k][d] = 0u;
+#pragma unroll
+            for (int ob = 0; ob < NB; ++ob) {
+                __builtin_amdgcn_sched_barrier(0);
+                f4 acc[4], act[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[t] = act[t] = z;
+                if (k == 0) {
+#pragma unroll
+                    for (int c = 0; c < O::L0_FULL; ++c) {
+                        const u4 av = reinterpret_cast<const u4 *>(lw + ob * O::L0_OB + c * O::OPB)[lane];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            const u4 bv = {b0[t][4 * c], b0[t][4 * c + 1], b0[t][4 * c + 2], b0[t][4 * c + 3]};
+                            acc[t] = Prec<P>::mma(av, bv, acc[t]);
+                            act[t] = Prec<P>::mma(bv, av, act[t]);
+                        }
                     }
+                    if constexpr (O::L0_HALF) {
+                        const u2 av = reinterpret_cast<const u2 *>(lw + ob * O::L0_OB + O::L0_FULL * O::OPB)[lane];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            const u2 bv = {b0[t][4 * O::L0_FULL], b0[t][4 * O::L0_FULL + 1]};
+                            acc[t] = Prec<P>::mma_half(av, bv, acc[t]);
+                            act[t] = Prec<P>::mma_half(bv, av, act[t]);
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int kb = 0; kb < KB; ++kb) {
+                        const u4 av = reinterpret_cast<const u4 *>(lw + ob * O::HROW + kb * O::OPB)[lane];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            const u4 bv = {bh[t][4 * kb], bh[t][4 * kb + 1], bh[t][4 * kb + 2], bh[t][4 * kb + 3]};
+                            acc[t] = Prec<P>::mma(av, bv, acc[t]);
+                            act[t] = Prec<P>::mma(bv, av, act[t]);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    bn[t][2 * ob] = Prec<P>::pack_relu(acc[t].x, acc[t].y);
+                    bn[t][2 * ob + 1] = Prec<P>::pack_relu(acc[t].z, acc[t].w);
+                    // (dword 2 t' + d of t = 2 h + t' sits at bit 8 h + 2 ob + d ...)
+                    mk[k][t >> 1] |= nonzero2(bn[t][2 * ob]) << (8 * (t & 1) + 2 * ob);
+                    mk[k][t >> 1] |= nonzero2(bn[t][2 * ob + 1]) << (8 * (t & 1) + 2 * ob + 1);
+                }
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    xt[k][ob][h] = (u4){Prec<P>::pack_relu(act[2 * h].x, act[2 * h].y),
+                                        Prec<P>::pack_relu(act[2 * h].z, act[2 * h].w),
+                                        Prec<P>::pack_relu(act[2 * h + 1].x, act[2 * h + 1].y),
+                                        Prec<P>::pack_relu(act[2 * h + 1].z, act[2 * h + 1].w)};
+                // packed here, not where the backward reads them (the unpacked
+                // sums of a layer would go to scratch)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    asm volatile("" : "+v"(xt[k][ob][h]));
+                    asm volatile("" : "+v"(mk[k][h]));
+                }
             }
 #pragma unroll
-            for (int k = S::H - 1; k >= 0; --k) {
-                const int dk = (k == 0) ? S::DIN : S::W;
-                const int woff = (k == 0) ? 0 : S::W * S::DIN + (k - 1) * S::W * S::W;
-                const int tb = B::tile_base(k);
+            for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int ob = 0; ob < B::NOB; ++ob)
+                for (int d = 0; d < S::W / 8; ++d) bh[t][d] = bn[t][d];
+        }
+        // ---- output, loss (Eq. 3) and d loss / dE of this lane's sample
+        float dEl[3];
+        {
+            f4 e[4] = {z, z, z, z};
+            const uint8_t *lw = fw + O::L0_BYTES + (S::H - 1) * O::HID_BYTES;
 #pragma unroll
-                    for (int ib = 0; ib < (S::DIN > S::W ? S::DIN : S::W) / 16; ++ib) {
-                        if (ib * 16 >= dk) break;
-                        const f4 v = dwacc[tb + ob * (dk / 16) + ib];
-                        float *dst = red + woff + (16 * ob + 4 * g) * dk + 16 * ib + j;
-                        dst[0] += v.x;
-                        dst[dk] += v.y;
-                        dst[2 * dk] += v.z;
-                        dst[3 * dk] += v.w;
-                    }
+            for (int kb = 0; kb < KB; ++kb) {
+                const u4 av = reinterpret_cast<const u4 *>(lw + kb * O::OPB)[lane];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const u4 bv = {bh[t][4 * kb], bh[t][4 * kb + 1], bh[t][4 * kb + 2], bh[t][4 * kb + 3]};
+                    e[t] = Prec<P>::mma(av, bv, e[t]);
+                }
+            }
+            // lane `lane` = sample_of(t, jj): channel c from lane jj of tile t
+            const int jj = 4 * ((lane >> 3) & 3) + (lane & 3), tt = 2 * (lane >> 5) + ((lane >> 2) & 1);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                float v[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float s = c == 0 ? e[t].x : c == 1 ? e[t].y : e[t].z;
+                    v[t] = u2f((uint32_t)__builtin_amdgcn_ds_bpermute(jj << 2, (int)f2u(s)));
+                }
+                const float Ev = tt == 0 ? v[0] : tt == 1 ? v[1] : tt == 2 ? v[2] : v[3];
+                dEl[c] = 0.0f;
+                if (work) {
+                    const float r = Ev - y[c], den = Ev * Ev + a.loss_eps;
+                    dEl[c] = 2.0f * r / den;
+                    lsum += r * r / den;
+                    bad |= !__builtin_isfinite(dEl[c]);
+                }
+                debuf[c * 64 + lane] = dEl[c];
             }
         }
-        __syncthreads();
+        wave_lds_fence();
+        // ---- backward: dW_H = dE X_H^T
+        u4 de[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
+        if (j < 3) {
+            de[0] = Mm<P>::h8(debuf + j * 64 + 8 * g);
+            de[1] = Mm<P>::h8(debuf + j * 64 + 32 + 8 * g);
+        }
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) dwacc[nb] = Prec<P>::mma(de[h], xt[S::H - 1][nb][h], dwacc[nb]);
+        // operand of the gradient that a layer hands down, per tile; first dE itself
+        uint32_t bg[4][S::W / 8];
+        u2 bo[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            bo[t] = (u2){0u, 0u};
+            if (g == 0) {
+                const int s = sample_of(t, j);
+                bo[t].x = Prec<P>::pack(debuf[s], debuf[64 + s]);
+                bo[t].y = Prec<P>::pack(debuf[128 + s], 0.f);
+            }
+        }
+        // layers k = H .. 1: the gradient of x_k from that of layer k's output,
+        // through x_k's ReLU, and dW_{k-1} from it
+#pragma unroll
+        for (int k = S::H; k >= 1; --k) {
+            uint32_t bn[4][S::W / 8];
+            const uint8_t *bk = bw + B::OUT_BYTES + (k - 1) * B::HID_BYTES;
+            constexpr int dk_max = IB > NB ? IB : NB;
+            const int dk = k == 1 ? IB : NB, tb = B::tile_base(k - 1);
+            u4 x0[dk_max][2];
+            if (k == 1) {
+#pragma unroll
+                for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        x0[ib][h] = *reinterpret_cast<const u4 *>(a.x_row + (chunk * S::DIN + 16 * ib + j) * 64 +
+                                                                  32 * h + 8 * g);
+            }
+#pragma unroll
+            for (int ob = 0; ob < NB; ++ob) {
+                __builtin_amdgcn_sched_barrier(0);
+                f4 gc[4], gt[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) gc[t] = gt[t] = z;
+                if (k == S::H) {
+                    const u2 av = reinterpret_cast<const u2 *>(bw + ob * B::OUT_OP)[lane];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        gc[t] = Prec<P>::mma_half(av, bo[t], z);
+                        gt[t] = Prec<P>::mma_half(bo[t], av, z);
+                    }
+                } else {
+#pragma unroll
+                    for (int kb = 0; kb < KB; ++kb) {
+                        const u4 av = reinterpret_cast<const u4 *>(bk + (ob * B::HOPS + kb) * B::OPB)[lane];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            const u4 bv = {bg[t][4 * kb], bg[t][4 * kb + 1], bg[t][4 * kb + 2], bg[t][4 * kb + 3]};
+                            gc[t] = Prec<P>::mma(av, bv, gc[t]);
+                            gt[t] = Prec<P>::mma(bv, av, gt[t]);
+                        }
+                    }
+                }
+                // through the ReLU, on the rounded halves
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int d = 0; d < 2; ++d) {
+                        const uint32_t m = (mk[k - 1][t >> 1] >> (8 * (t & 1) + 2 * ob + d)) & 0x00010001u;
+                        bn[t][2 * ob + d] = keep2(d ? Prec<P>::pack(gc[t].z, gc[t].w) : Prec<P>::pack(gc[t].x, gc[t].y), m);
+                    }
+                u4 gv[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const u4 xv = xt[k - 1][ob][h];
+                    gv[h].x = keep2(Prec<P>::pack(gt[2 * h].x, gt[2 * h].y), nonzero2(xv.x));
+                    gv[h].y = keep2(Prec<P>::pack(gt[2 * h].z, gt[2 * h].w), nonzero2(xv.y));
+                    gv[h].z = keep2(Prec<P>::pack(gt[2 * h + 1].x, gt[2 * h + 1].y), nonzero2(xv.z));
+                    gv[h].w = keep2(Prec<P>::pack(gt[2 * h + 1].z, gt[2 * h + 1].w), nonzero2(xv.w));
+                }
+#pragma unroll
+                for (int ib = 0; ib < dk_max; ++ib) {
+                    if (ib >= dk) break;
+                    f4 &acc = dwacc[tb + ob * dk + ib];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        acc = Prec<P>::mma(gv[h], k == 1 ? x0[ib][h] : xt[k >= 2 ? k - 2 : 0][ib < NB ? ib : 0][h], acc);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int d = 0; d < S::W / 8; ++d) bg[t][d] = bn[t][d];
+        }
+        // ---- gradient of the grid features, rows 16 ib + 4 g + r of sample_of(t, j),
+        // through LDS (rows of 2L floats padded by two) out as [chunk][level][64] pairs
+        {
+            float *dx = reinterpret_cast<float *>(wbuf);
+            const uint8_t *bk = bw + B::OUT_BYTES + (S::H - 1) * B::HID_BYTES;
+#pragma unroll
+            for (int ib = 0; ib < B::GIB; ++ib) {
+                __builtin_amdgcn_sched_barrier(0);
+                f4 gc[4] = {z, z, z, z};
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb) {
+                    const u4 av = reinterpret_cast<const u4 *>(bk + (ib * B::HOPS + kb) * B::OPB)[lane];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const u4 bv = {bg[t][4 * kb], bg[t][4 * kb + 1], bg[t][4 * kb + 2], bg[t][4 * kb + 3]};
+                        gc[t] = Prec<P>::mma(av, bv, gc[t]);
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    float *d = dx + sample_of(t, j) * B::NFP + 16 * ib + 4 * g;
+                    d[0] = gc[t].x; d[1] = gc[t].y; d[2] = gc[t].z; d[3] = gc[t].w;
+                }
+            }
+            wave_lds_fence();
+            const bool scatter = live && pos_ok && (dEl[0] != 0.f || dEl[1] != 0.f || dEl[2] != 0.f) &&
+                                 __builtin_isfinite(dEl[0]) && __builtin_isfinite(dEl[1]) && __builtin_isfinite(dEl[2]);
+            if (live) {
+                const float2 *mine = reinterpret_cast<const float2 *>(dx + lane * B::NFP);
+                float2 *dst = reinterpret_cast<float2 *>(a.dx0) + chunk * 64 * S::L + lane;
+#pragma unroll
+                for (int l = 0; l < S::L; ++l) {
+                    const float2 v = mine[l];
+                    dst[l * 64] = v;
+                    if (scatter) gmax = fmaxf(gmax, fmaxf(fabsf(v.x), fabsf(v.y)));
+                }
+                a.sflag[q] = scatter ? 1 : 0;
+            }
+            wave_lds_fence();   // the block is written again for the next chunk
+        }
     }
-    float *row = a.dw_part + (int64_t)blockIdx.x * B::NMLP;
-    for (int k = threadIdx.x; k < B::NMLP; k += 256) row[k] = red[k];
+    if (__ballot(bad) != 0ull && lane == 0) atomicOr(a.status + 2, 1u);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off);
+    if (lane == 0) atomicAdd(a.loss, lsum * a.loss_scale);
+    grad_bound(gmax, a.loss_scale, a.status, lane);
+    store_weight_gradient<P, S>(dwacc, smem, a.dw_part, wave, g, j);
 }
 
 // Column sums of the per-workgroup weight gradients, scaled, into the
@@ -1178,6 +1567,31 @@ struct SideFork {
     }
 };
 
+// Workgroups of a kernel with this much dynamic LDS that the device holds at
+// once (asked once per kernel).
+struct Resident {
+    std::atomic<int64_t> n{0};
+    template <class K> hipError_t get(K kern, int threads, size_t lds, int64_t *out)
+    {
+        int64_t v = n.load();
+        if (v == 0) {
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+            int dev = 0, n_cu = 0, nb = 0;
+            if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
+            if ((e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
+                return e;
+            if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, threads, lds)) != hipSuccess)
+                return e;
+            v = (int64_t)(nb > 0 ? nb : 1) * n_cu;
+            n.store(v);
+        }
+        *out = v;
+        return hipSuccess;
+    }
+};
+
 template <int P, class S>
 static hipError_t backward_t(const Model &m, const niv_batch &b, const niv_train_state &st,
                              hipStream_t stream)
@@ -1263,86 +1677,86 @@ static hipError_t backward_t(const Model &m, const niv_batch &b, const niv_train
     hipLaunchKernelGGL(k_grid_count, dim3(kScatterBlocks), dim3(kScatterThreads), 0, side, sa);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = hipEventRecord(ev.join, side)) != hipSuccess) return e;
-    // FP16: grid level 0, when dense and at most kL0Words entries, is read
-    // from LDS (its random-sample gathers would touch a line per lane)
-    if (P == NIV_FP16 && m.cfg.n_levels > 0 && m.dense[0] && m.size[0] <= kL0Words) {
-        a.l0_words = (uint32_t)m.size[0];
-        a.l0_off = (uint32_t)m.offset[0];
-    }
-    {
+    // 1./2. forward, loss and backward
+    const int64_t n_chunks = (b.count + 63) / 64;
+    float *dw_part = reinterpret_cast<float *>(ws + L.dw_off);
+    float *dx0 = reinterpret_cast<float *>(ws + L.dx0_off);
+    int64_t bwd_blocks = 0;   // workgroups that write a row of weight gradients
+    if constexpr (P == NIV_FP16) {
+        EncodeArgs ea;
+        memset(&ea, 0, sizeof(ea));
+        ea.x = b.x;
+        ea.nrm = b.nrm;
+        ea.extra = b.extra;
+        ea.valid = b.valid;
+        ea.model = a.f[0].model;
+        ea.grid_off = a.grid_off;
+        ea.grid_bytes = a.grid_bytes;
+        ea.hash_mask = a.hash_mask;
+        ea.x_pair = reinterpret_cast<uint32_t *>(ws + L.x_off);
+        ea.x_row = reinterpret_cast<uint16_t *>(ws + L.x_off + n_chunks * S::DIN * 128);
+        ea.n = b.count;
+        for (int c = 0; c < 3; ++c) { ea.lo[c] = a.lo[c]; ea.hi[c] = a.hi[c]; }
+        hipLaunchKernelGGL(k_train_encode<S>, dim3((unsigned)(kXcds * ((n_chunks + kEncWaves - 1) / kEncWaves))),
+                           dim3(64 * kEncWaves), 0, stream, ea);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        MlpArgs ma;
+        memset(&ma, 0, sizeof(ma));
+        ma.fwd = a.f[0].model + kLevelBytes;
+        ma.bwd = ws + L.bwd_off;
+        ma.x_pair = ea.x_pair;
+        ma.x_row = ea.x_row;
+        ma.x = b.x;
+        ma.nrm = b.nrm;
+        ma.extra = b.extra;
+        ma.target = b.target;
+        ma.valid = b.valid;
+        ma.dw_part = dw_part;
+        ma.dx0 = dx0;
+        ma.sflag = ws + L.sflag_off;
+        ma.status = status;
+        ma.loss = st.loss;
+        ma.n = b.count;
+        ma.loss_scale = a.loss_scale;
+        ma.loss_eps = a.loss_eps;
+        static Resident res;
+        if ((e = res.get(k_train_mlp<S>, 256, B::MLP_LDS, &bwd_blocks)) != hipSuccess) return e;
+        bwd_blocks = std::min(std::min<int64_t>(bwd_blocks, kBwdMaxBlocks), (n_chunks + 3) / 4);
+        hipLaunchKernelGGL(k_train_mlp<S>, dim3((unsigned)bwd_blocks), dim3(256), (size_t)B::MLP_LDS, stream, ma);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    } else {
         constexpr int kBlock = 256, kWavesPerBlock = 4;
-        auto kern = k_query<P, S, true, 4, true, kBlock>;
-        const size_t lds = O::W_BYTES + (size_t)kWavesPerBlock * 64 * O::ROW_DW * 4 +
-                           (P == NIV_FP16 ? (size_t)kL0Words * 4 : 0);
-        static int max_blocks = -1, n_cu = 0;
-        if (max_blocks < 0) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-            int dev = 0;
-            if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
-            if ((e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
-                return e;
-            int nb = 0;
-            if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, kBlock, lds)) != hipSuccess)
-                return e;
-            max_blocks = nb > 0 ? nb : 1;
-        }
-        const int64_t n_chunks = (b.count + 63) / 64;
+        auto fwd = k_query<P, S, true, 4, true, kBlock>;
+        const size_t fwd_lds = O::W_BYTES + (size_t)kWavesPerBlock * 64 * O::ROW_DW * 4;
+        static Resident fres, bres;
+        int64_t fwd_blocks = 0;
+        if ((e = fres.get(fwd, kBlock, fwd_lds, &fwd_blocks)) != hipSuccess) return e;
         a.n_tiles = (n_chunks + kWavesPerBlock - 1) / kWavesPerBlock;
-        int64_t blocks = a.n_tiles < (int64_t)max_blocks * n_cu ? a.n_tiles : (int64_t)max_blocks * n_cu;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(blocks < 1 ? 1 : blocks)), dim3(kBlock), lds, stream, a);
+        fwd_blocks = std::min<int64_t>(a.n_tiles, fwd_blocks);
+        hipLaunchKernelGGL(fwd, dim3((unsigned)fwd_blocks), dim3(kBlock), fwd_lds, stream, a);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        BwdArgs ba;
+        memset(&ba, 0, sizeof(ba));
+        ba.bwd = ws + L.bwd_off;
+        ba.x_save = ws + L.x_off;
+        ba.mask_save = reinterpret_cast<const uint32_t *>(ws + L.mask_off);
+        ba.dE = reinterpret_cast<const float *>(ws + L.dE_off);
+        ba.x = b.x;
+        ba.dw_part = dw_part;
+        ba.dx0 = dx0;
+        ba.sflag = ws + L.sflag_off;
+        ba.vmax = status;
+        ba.n = b.count;
+        ba.loss_scale = a.loss_scale;
+        if ((e = bres.get(k_train_bwd<S>, 256, (size_t)B::LDS_BYTES, &bwd_blocks)) != hipSuccess) return e;
+        bwd_blocks = std::min(std::min<int64_t>(bwd_blocks, kBwdMaxBlocks), (n_chunks + 3) / 4);
+        hipLaunchKernelGGL(k_train_bwd<S>, dim3((unsigned)bwd_blocks), dim3(256), (size_t)B::LDS_BYTES, stream, ba);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    // 2. backward
-    BwdArgs ba;
-    memset(&ba, 0, sizeof(ba));
-    ba.bwd = ws + L.bwd_off;
-    ba.x_save = ws + L.x_off;
-    ba.mask_save = reinterpret_cast<const uint32_t *>(ws + L.mask_off);
-    ba.dE = reinterpret_cast<const float *>(ws + L.dE_off);
-    ba.x = b.x;
-    ba.model = static_cast<const uint8_t *>(st.model);
-    const float loss_scale = (float)(1.0 / (3.0 * (double)b.count));
-    ba.grads = st.grads;
-    ba.dw_part = reinterpret_cast<float *>(ws + L.dw_off);
-    ba.dx0 = reinterpret_cast<float *>(ws + L.dx0_off);
-    ba.sflag = ws + L.sflag_off;
-    ba.vmax = status;
-    ba.n = b.count;
-    ba.n_grid = m.n_grid_values;
-    ba.loss_scale = loss_scale;
-    ba.hash_mask = a.hash_mask;
-    for (int c = 0; c < 3; ++c) { ba.lo[c] = a.lo[c]; ba.hi[c] = a.hi[c]; }
-    {
-        auto kern = k_train_bwd<P, S>;
-        const size_t lds = (size_t)B::LDS_BYTES;
-        static int max_blocks = -1, n_cu = 0;
-        if (max_blocks < 0) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-            int dev = 0;
-            if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
-            if ((e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
-                return e;
-            int nb = 0;
-            if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, 256, lds)) != hipSuccess)
-                return e;
-            max_blocks = nb > 0 ? nb : 1;
-        }
-        const int64_t n_chunks = (b.count + 63) / 64;
-        int64_t blocks = (n_chunks + 3) / 4;
-        blocks = blocks < (int64_t)max_blocks * n_cu ? blocks : (int64_t)max_blocks * n_cu;
-        blocks = blocks < kBwdMaxBlocks ? blocks : kBwdMaxBlocks;
-        blocks = blocks < 1 ? 1 : blocks;
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), lds, stream, ba);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        // weight gradient: the workgroups' rows summed, one row per workgroup
-        hipLaunchKernelGGL(k_dw_sum, dim3((unsigned)((B::NMLP + 15) / 16)), dim3(256), 0, stream, ba.dw_part,
-                           (int64_t)B::NMLP, (int)blocks, st.grads + m.n_grid_values, ba.loss_scale);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+    // weight gradient: the workgroups' rows summed
+    hipLaunchKernelGGL(k_dw_sum, dim3((unsigned)((B::NMLP + 15) / 16)), dim3(256), 0, stream, dw_part,
+                       (int64_t)B::NMLP, (int)bwd_blocks, st.grads + m.n_grid_values, a.loss_scale);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     // 3. grid scatter through bins (counted beside the forward, above)
     if ((e = hipStreamWaitEvent(stream, ev.join, 0)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_grid_scan_bins, dim3(sa.cstride / 4), dim3(kScatterBlocks), 0, stream, sa);

@@ -390,3 +390,33 @@ def test_full_batch_gradient_is_the_sum_of_its_halves():
         mx = np.abs(a - b).max() / np.abs(a).max()
         print(f"  {name}: rel-L2 {rel:.2e}, max/max {mx:.2e}", flush=True)
         assert rel <= 1e-5 and mx <= 1e-4, (name, rel, mx)
+
+
+@pytest.mark.parametrize("wname", ["unit_cube_16k", "room_1080p", "room_train_6d"])
+@pytest.mark.parametrize("n", [63, 65, 257, 65536 + 4133])
+def test_fp16_gradient_at_ragged_counts(wname, n):
+    """The FP16 gradient pass where its waves have less than one chunk of 64
+    samples, one and a few, and more chunks than the device holds waves
+    (1024), with samples left out by the valid flags, by a position that is
+    not finite and by a zero normal.  Samples near a ReLU tie are left out:
+    a 16-bit pre-activation of the third layer carries at most the roundings
+    of three layers, 2^-11 of its terms each, so 2e-3 keeps the FP64
+    decisions.  Targets well away from the outputs (within 1.5), so that
+    d loss / dE has no cancellation; then every value is good to the bars of
+    the file."""
+    w, oc, params, x, nrm, _ = _setup(wname, n, seed=11)
+    rng = np.random.default_rng(12)
+    tgt = rng.uniform(3.0, 5.0, size=(n, 3)).astype(np.float32)
+    extra = rng.uniform(0, 1, size=(n, oc.n_extra)).astype(np.float32) if oc.n_extra else None
+    p16 = params.astype(np.float16).astype(np.float64)
+    ok = _clear_of_ties(oc, p16, x, nrm, extra=extra, margin=2e-3)
+    xg, ng, vd, vref = x.copy(), nrm.copy(), ok.copy(), ok.copy()
+    xg[3::29, 1] = np.nan
+    ng[5::31] = 0.0
+    vd[7::37] = 0
+    vref[3::29] = vref[5::31] = vref[7::37] = 0
+    assert vref.any()
+    loss, g = _gpu_grad(w, params, xg, ng, tgt, "fp16", valid=vd, extra=extra)
+    l_ref, g_ref = O.loss_grad(oc, p16, x, nrm, tgt, valid=vref, **({} if extra is None else {"extra": extra}))
+    assert loss == pytest.approx(l_ref, rel=5e-3)
+    _compare(oc, g, g_ref, 2e-2, grid_bar=3e-2)
