@@ -956,18 +956,36 @@ struct ScatterArgs {
     int64_t n, n_entries;
     int32_t n_levels, n_bins;
     int32_t cstride;           // row length of counts: n_bins rounded up to 4
+    int32_t parts_shift;       // log2 of the workgroups that share a group's chunks, see scatter_parts_shift
     uint32_t hash_mask;
     float loss_scale;
     double lo[3], hi[3];
 };
 
-// Both passes: one wave takes a 64-sample chunk through every level (the
-// level is wave-uniform, so its constants are scalar loads); workgroup b
-// takes chunks kScatterWaves b + w, strided by kScatterWaves x the grid, in
-// both passes, so a workgroup writes exactly the records it counted.
+// Both passes: one wave takes a 64-sample chunk through its levels (the
+// level is wave-uniform, so its constants are scalar loads).  Workgroup b is
+// part b mod parts of group b / parts: the group takes chunks kScatterWaves g
+// + w, strided by kScatterWaves x the groups, and the part its share of the
+// levels, in both passes, so a workgroup writes exactly the records it
+// counted.
 constexpr int kScatterWaves = 8;
 constexpr int kScatterThreads = 64 * kScatterWaves;
 constexpr int kScatterMaxLevels = 16;          // levels of the trainable shapes
+
+// A batch with fewer groups than workgroups gives the rest of them a part of
+// the levels: the passes are a chain over a workgroup's levels, so a batch of
+// 64 chunks took as long to write as one of 1024 (51 and 55 us; now 11 and
+// 29 us, and 2048 chunks 45 us where they took 58).  A batch of more than
+// half as many groups keeps one part: there every workgroup has a whole
+// chain, and two on a CU fill each other's gaps (1024 workgroups with half
+// the levels each: 129 us against 73 at 2^18 samples).
+static int scatter_parts_shift(int64_t n, int n_levels)
+{
+    const int64_t groups = ((n + 63) / 64 + kScatterWaves - 1) / kScatterWaves;
+    int s = 0;
+    while ((1 << (s + 1)) <= n_levels && (groups << (s + 1)) <= kScatterBlocks) ++s;
+    return s;
+}
 
 // Inclusive scan over the 64 lanes of a wave.
 __device__ inline uint32_t wave_scan_incl(uint32_t v, int lane)
@@ -1008,11 +1026,12 @@ __global__ __launch_bounds__(kScatterThreads) void k_grid_count(const ScatterArg
     __syncthreads();
     const int64_t n_chunks = (a.n + 63) / 64;
     ConstLevels lvs = (ConstLevels)a.model;
-    for (int64_t chunk = (int64_t)blockIdx.x * kScatterWaves + wave; chunk < n_chunks;
-         chunk += (int64_t)gridDim.x * kScatterWaves) {
+    const int part = blockIdx.x & ((1 << a.parts_shift) - 1), n_part = a.n_levels >> a.parts_shift;
+    for (int64_t chunk = (int64_t)(blockIdx.x >> a.parts_shift) * kScatterWaves + wave; chunk < n_chunks;
+         chunk += (int64_t)(gridDim.x >> a.parts_shift) * kScatterWaves) {
         double p[3];
         if (!scatter_sample(a, chunk * 64 + lane, p)) continue;
-        for (int l = 0; l < a.n_levels; ++l) {
+        for (int l = part * n_part; l < (part + 1) * n_part; ++l) {
             uint32_t idx[8];
             float w[8];
             level_corners(lvs[l], p, a.hash_mask, idx, w);
@@ -1036,24 +1055,27 @@ __global__ __launch_bounds__(kScatterThreads) void k_grid_count(const ScatterArg
 // Write pass.  The waves of a workgroup order the records of their chunks
 // at one level together, so that each bin receives one run of consecutive
 // slots per workgroup (~128 records on a hashed level of 2^17 entries, for
-// 8 chunks of 64 samples): per window of 64 of the level's bins, a histogram in LDS
+// 8 chunks of 64 samples): per window of the level's bins, a histogram in LDS
 // gives each record its rank in its bin, one wave scans the histogram and
 // reserves each bin's run in the workgroup's segment of that bin, the
 // records are staged in that order, and the workgroup stores them with
 // consecutive threads on consecutive slots.  The feature gradients of a
 // chunk are read one level at a time with a coalesced load (the backward
-// stores them level-major per chunk).
+// stores them level-major per chunk).  Bound by this chain, four barriers a
+// level, up to 2^17 samples (see scatter_parts_shift) and by the bytes
+// written in FP32 beyond (2^18 samples: 85 us for 335 MB).
 // H16 (the FP16 training path): records carry the contributions as an FP16
 // pair scaled by 2^(14 - e), M < 2^e, so every value is below 2^14 and keeps
 // 11 significant bits (the operands of that path are FP16 already); 6 bytes
 // per record instead of 10.
 template <bool H16>
-__global__ __launch_bounds__(kScatterThreads) void k_grid_write(const ScatterArgs a)
+__global__ __launch_bounds__(kScatterThreads)
+void k_grid_write(const ScatterArgs a)
 {
     // staged records: (bin in the window << 16 | entry within the bin) and
     // the value(s)
     using Val = typename std::conditional<H16, uint32_t, uint2>::type;
-    constexpr int kWindow = 64;                     // bins ordered per pass
+    constexpr int kLaneBins = 3, kWindow = 64 * kLaneBins;   // bins ordered per pass: a level of up to 2^19 entries
     __shared__ uint32_t cnt[kMaxBins];              // next free slot of each bin's segment
     __shared__ uint32_t hist[kWindow], lst[kWindow], gofs[kWindow];
     __shared__ uint32_t s_total;
@@ -1125,7 +1147,7 @@ __global__ __launch_bounds__(kScatterThreads) void k_grid_write(const ScatterArg
         }
         if (blockIdx.x == 0 && t == kScatterThreads - 1) a.split[a.n_bins] = s2;
     }
-    if (t < kWindow) hist[t] = 0u;
+    for (int k = t; k < kWindow; k += kScatterThreads) hist[k] = 0u;
     __syncthreads();
     if (blockIdx.x == 0 && t == 0) a.vmax[1] = s_max;
     const int64_t n_chunks = (a.n + 63) / 64;
@@ -1136,9 +1158,11 @@ __global__ __launch_bounds__(kScatterThreads) void k_grid_write(const ScatterArg
         (void)frexpf(u2f(a.vmax[0]), &e);
         rs = ldexpf(1.0f, 14 - e);
     }
+    const int part = blockIdx.x & ((1 << a.parts_shift) - 1), n_part = L >> a.parts_shift;
+    const int lb = part * n_part, le = lb + n_part;
     // the iteration count is uniform over the workgroup (barriers inside)
-    for (int64_t g0 = (int64_t)blockIdx.x * kScatterWaves; g0 < n_chunks;
-         g0 += (int64_t)gridDim.x * kScatterWaves) {
+    for (int64_t g0 = (int64_t)(blockIdx.x >> a.parts_shift) * kScatterWaves; g0 < n_chunks;
+         g0 += (int64_t)(gridDim.x >> a.parts_shift) * kScatterWaves) {
         const int64_t chunk = g0 + wave;
         const int64_t q0 = chunk * 64;
         const float2 *src = reinterpret_cast<const float2 *>(a.dx0) + q0 * L + lane;
@@ -1146,10 +1170,10 @@ __global__ __launch_bounds__(kScatterThreads) void k_grid_write(const ScatterArg
         const bool live = chunk < n_chunks && scatter_sample(a, q0 + lane, p);
         const bool sc = live && a.sflag[q0 + lane] != 0;   // else the records carry zeros
         // the next level's feature gradients are loaded while a level is ordered
-        float2 gn = sc ? src[0] : make_float2(0.0f, 0.0f);
-        for (int l = 0; l < L; ++l) {
+        float2 gn = sc ? src[lb * 64] : make_float2(0.0f, 0.0f);
+        for (int l = lb; l < le; ++l) {
             const float2 gg = gn;
-            if (l + 1 < L) gn = sc ? src[(l + 1) * 64] : make_float2(0.0f, 0.0f);
+            if (l + 1 < le) gn = sc ? src[(l + 1) * 64] : make_float2(0.0f, 0.0f);
             uint32_t idx[8];
             float w[8];
             level_corners(lvs[l], p, a.hash_mask, idx, w);
@@ -1168,17 +1192,28 @@ __global__ __launch_bounds__(kScatterThreads) void k_grid_write(const ScatterArg
                 __syncthreads();
                 if (wave == 0) {
                     // runs of the window's bins: a bin with records is a bin of
-                    // this level, so its cursor exists; one lane per bin
-                    const uint32_t nb = hist[lane];
-                    const uint32_t incl = wave_scan_incl(nb, lane);
-                    uint32_t base = 0u;
-                    if (nb) {
-                        base = cnt[fb + w0 + lane];
-                        cnt[fb + w0 + lane] = base + nb;
+                    // this level, so its cursor exists
+                    uint32_t nb[kLaneBins], sum = 0u;
+#pragma unroll
+                    for (int k = 0; k < kLaneBins; ++k) {
+                        nb[k] = hist[kLaneBins * lane + k];
+                        sum += nb[k];
                     }
-                    lst[lane] = incl - nb;
-                    gofs[lane] = base - (incl - nb);   // slot of staged record k: gofs[bin] + k
-                    hist[lane] = 0u;
+                    const uint32_t incl = wave_scan_incl(sum, lane);
+                    uint32_t at = incl - sum;
+#pragma unroll
+                    for (int k = 0; k < kLaneBins; ++k) {
+                        const int i = kLaneBins * lane + k;
+                        uint32_t base = 0u;
+                        if (nb[k]) {
+                            base = cnt[fb + w0 + i];
+                            cnt[fb + w0 + i] = base + nb[k];
+                        }
+                        lst[i] = at;
+                        gofs[i] = base - at;   // slot of staged record k: gofs[bin] + k
+                        hist[i] = 0u;
+                        at += nb[k];
+                    }
                     if (lane == 63) s_total = incl;
                 }
                 __syncthreads();
@@ -1263,7 +1298,11 @@ __device__ inline int fixed_shift(const uint32_t *vmax)
 // work_start[b] workgroups of at most kAccumRecords records.  Each sums its
 // share in LDS in 64-bit fixed point at the step's scale (fixed_shift; LDS
 // integer atomics run far faster than LDS float atomics here, and integer
-// sums do not depend on the order).  A bin taken by one workgroup is stored
+// sums do not depend on the order).  The atomics bound it: each feature has
+// its own array, so that a wave's adds spread over 32 bank pairs (16 with the
+// two features side by side), and the records come four to a load.  2^18
+// samples of the room network, FP16: 56 -> 46 us, FP32: 80 -> 74 us; 2^16:
+// 35 -> 28 us.  A bin taken by one workgroup is stored
 // as is (every entry, zeros included); a shared bin (the coarse dense
 // levels) stores each part's integer sums, which k_grid_merge adds.
 template <bool H16>
@@ -1306,39 +1345,67 @@ __global__ __launch_bounds__(1024) void k_grid_accum(const ScatterArgs a)
             return a.vals[r];
         }
     };
-    uint32_t r = r0 + threadIdx.x;
-    // eight records per thread in flight before the LDS adds
-    for (; r + 7 * 1024 < r1; r += 8 * 1024) {
-        uint32_t i[8];
-        float2 v[8];
+    auto add = [&](uint32_t i, float2 v) {
+        atomicAdd(&acc[i], fx(v.x));
+        atomicAdd(&acc[kBinEntries + i], fx(v.y));
+    };
+    // four records per thread and load, two loads in flight; the ends singly
+    const uint32_t ra = (r0 + 3u) & ~3u, rz = r1 & ~3u;
+    if (ra < rz) {
+        if (threadIdx.x < ra - r0) add(a.keys[r0 + threadIdx.x], val(r0 + threadIdx.x));
+        if (threadIdx.x < r1 - rz) add(a.keys[rz + threadIdx.x], val(rz + threadIdx.x));
+        auto quad = [&](uint32_t r, u2 &k, u4 (&v)[H16 ? 1 : 2]) {
+            k = *reinterpret_cast<const u2 *>(a.keys + r);
+            if constexpr (H16) {
+                v[0] = *reinterpret_cast<const u4 *>(a.vals16 + r);
+            } else {
+                v[0] = reinterpret_cast<const u4 *>(a.vals + r)[0];
+                v[1] = reinterpret_cast<const u4 *>(a.vals + r)[1];
+            }
+        };
+        auto add4 = [&](u2 k, const u4 (&v)[H16 ? 1 : 2]) {
+            const uint32_t i[4] = {k.x & 0xffffu, k.x >> 16, k.y & 0xffffu, k.y >> 16};
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            i[k] = a.keys[r + k * 1024];
-            v[k] = val(r + k * 1024);
+            for (int u = 0; u < 4; ++u) {
+                float2 f;
+                if constexpr (H16) {
+                    const f2 h = Prec<NIV_FP16>::unpack(v[0][u]);
+                    f = make_float2(h.x, h.y);
+                } else {
+                    f = make_float2(u2f(v[u / 2][2 * (u & 1)]), u2f(v[u / 2][2 * (u & 1) + 1]));
+                }
+                add(i[u], f);
+            }
+        };
+        uint32_t r = ra + 4 * threadIdx.x;
+        for (; r + 4096 < rz; r += 2 * 4096) {
+            u2 k0, k1;
+            u4 v0[H16 ? 1 : 2], v1[H16 ? 1 : 2];
+            quad(r, k0, v0);
+            quad(r + 4096, k1, v1);
+            add4(k0, v0);
+            add4(k1, v1);
         }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            atomicAdd(&acc[2 * i[k]], fx(v[k].x));
-            atomicAdd(&acc[2 * i[k] + 1], fx(v[k].y));
+        if (r < rz) {
+            u2 k0;
+            u4 v0[H16 ? 1 : 2];
+            quad(r, k0, v0);
+            add4(k0, v0);
         }
-    }
-    for (; r < r1; r += 1024) {
-        const uint32_t i = a.keys[r];
-        const float2 v = val(r);
-        atomicAdd(&acc[2 * i], fx(v.x));
-        atomicAdd(&acc[2 * i + 1], fx(v.y));
+    } else {
+        for (uint32_t r = r0 + threadIdx.x; r < r1; r += 1024) add(a.keys[r], val(r));
     }
     __syncthreads();
     const int64_t e0 = (int64_t)b << kBinShift;
     if (parts > 1) {
         long long *dst = a.parts + (int64_t)w * (2 * kBinEntries);
-        for (int k = threadIdx.x; k < 2 * kBinEntries; k += 1024) dst[k] = (long long)acc[k];
+        for (int k = threadIdx.x; k < 2 * kBinEntries; k += 1024) dst[k] = (long long)acc[(k & 1) * kBinEntries + (k >> 1)];
         return;
     }
     for (int k = threadIdx.x; k < 2 * kBinEntries; k += 1024) {
         const int64_t en = e0 + (k >> 1);
         if (en >= a.n_entries) continue;
-        a.grads[2 * en + (k & 1)] = (float)((double)(long long)acc[k] * down);
+        a.grads[2 * en + (k & 1)] = (float)((double)(long long)acc[(k & 1) * kBinEntries + (k >> 1)] * down);
     }
 }
 
@@ -1663,6 +1730,7 @@ static hipError_t backward_t(const Model &m, const niv_batch &b, const niv_train
     sa.loss_scale = (float)(1.0 / (3.0 * (double)b.count));
     for (int c = 0; c < 3; ++c) { sa.lo[c] = a.lo[c]; sa.hi[c] = a.hi[c]; }
     sa.cstride = (sa.n_bins + 3) & ~3;
+    sa.parts_shift = scatter_parts_shift(b.count, sa.n_levels);
     if (sa.n_bins > kMaxBins) return hipErrorInvalidValue;
     if (sa.n_levels > kScatterMaxLevels) return hipErrorInvalidValue;
     // the count pass reads only the batch and the level table: it runs on a
