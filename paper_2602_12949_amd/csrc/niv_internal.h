@@ -65,17 +65,6 @@ struct QueryArgs {
     uint32_t *fb_list;        // fallback list: (frame << 28) | pixel, or null
     uint32_t *fb_count;       // entries appended (may exceed fb_cap)
     uint32_t fb_cap;
-    float loss_scale;         // training: 1/(3n)
-    // FP32 training forward only (the fused kernel instantiated with TRAIN, frame 0):
-    const float *extra_ps;    // per-sample scene variables [count][n_extra] or null
-    const float *target;      // [count][3] irradiance targets
-    const uint8_t *valid;     // [count] or null
-    uint8_t *x_save;          // activations, per 64-sample chunk [rows][64]
-    uint32_t *mask_save;      // ReLU masks, per chunk, layer, dword, lane
-    float *dE;                // [count][3] d(loss)/dE without the 1/(3n) factor
-    float *loss;              // device scalar, accumulates the Eq. 3 loss
-    uint32_t *train_status;   // step words of the training scratch; [2] set by a non-finite dE
-    float loss_eps;           // 0.01 (Eq. 3)
     int32_t xcd_order;        // tile order, see LaunchTune
     FrameArgs f[kMaxFrames];
 };

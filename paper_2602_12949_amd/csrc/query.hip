@@ -173,7 +173,7 @@ static hipError_t query_t(QueryArgs &a, const LaunchTune &tu, hipStream_t st)
     // a smaller workgroup than the instantiation's runs the same kernel
     const int threads = (BLOCK == 256 && tu.block < BLOCK) ? tu.block : BLOCK;
     const int waves = threads / 64;
-    auto kern = k_query<P, S, WLDS, TB, false, BLOCK, PROBE>;
+    auto kern = k_query<P, S, WLDS, TB, BLOCK, PROBE>;
     constexpr size_t lds = query_lds<P, S, WLDS, BLOCK>();
     static_assert(lds <= kLdsPerCu, "workgroup LDS");
     static int max_blocks = -1;  // resident workgroups per CU for this instantiation

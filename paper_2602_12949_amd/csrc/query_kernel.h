@@ -43,19 +43,15 @@ template <int P, class S> constexpr int query_min_waves()
 // PROBE (measurement only): the encoding stage alone, with the launch shape,
 // pixel order and encoding functions of the query, writing one word per
 // pixel (E[3q]) instead of running the network.
-template <int P, class S, bool WLDS, int TB, bool TRAIN, int BLOCK, bool PROBE = false>
+template <int P, class S, bool WLDS, int TB, int BLOCK, bool PROBE = false>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(query_min_waves<P, S>())))
 void k_query(const QueryArgs a)
 {
-    static_assert(!PROBE || (!TRAIN && !S::SL), "probe: staged query encoding");
+    static_assert(!PROBE || !S::SL, "probe: staged query encoding");
     // BLOCK threads at most; small calls launch 64 or 128
     const int n_threads = BLOCK > 256 ? BLOCK : (int)blockDim.x, n_waves = n_threads / 64;
     using O = Ops<P, S>;
-    static_assert(!TRAIN || (TB == 4 && P == NIV_FP32), "training: four tiles, FP32 (FP16: k_train_mlp)");
     static_assert(!S::SL || WLDS, "lane slices read the level table from LDS");
-    static_assert(!TRAIN || S::DIN == S::DIN_IN, "training: kernel columns are the parameter columns");
-    // training saves: per 64-sample chunk, X_0 (DIN rows) then X_1..X_H (W rows), each [row][64]
-    constexpr int64_t CHUNK_BYTES = (int64_t)(S::DIN + S::H * S::W) * 64 * O::ES;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -286,14 +282,11 @@ void k_query(const QueryArgs a)
                 }
             }
         };
-        if constexpr (S::SL) {
-            static_assert(!TRAIN, "training uses the staged encoding");
-        } else {
+        if constexpr (!S::SL) {
         // ---- 1. load and encode this lane's pixel
         float px = 0.f, py = 0.f, pz = 0.f, nx = 0.f, ny = 0.f, nz = 0.f;
         if (live) {
             on = f_mask ? (f_mask[qs] != 0) : true;
-            if constexpr (TRAIN) on = a.valid ? (a.valid[q] != 0) : true;
             if (on) {
                 px = f_pos[3 * qs]; py = f_pos[3 * qs + 1]; pz = f_pos[3 * qs + 2];
                 nx = f_nrm[3 * qs]; ny = f_nrm[3 * qs + 1]; nz = f_nrm[3 * qs + 2];
@@ -302,22 +295,8 @@ void k_query(const QueryArgs a)
         bool bad = !(__builtin_isfinite(px) && __builtin_isfinite(py) && __builtin_isfinite(pz) &&
                      __builtin_isfinite(nx) && __builtin_isfinite(ny) && __builtin_isfinite(nz));
         if constexpr (S::NEX > 0) {
-            if (TRAIN && a.extra_ps) {
 #pragma unroll
-                for (int e = 0; e < S::NEX; ++e) {
-                    const float te = live ? a.extra_ps[q * S::NEX + e] : 0.0f;
-                    bad |= !__builtin_isfinite(te);
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        float t = te * (float)(1 << k);
-                        gam[16 * e + 2 * k] = sinpif(t);
-                        gam[16 * e + 2 * k + 1] = cospif(t);
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < S::NEX; ++e) bad |= !__builtin_isfinite(ka->f[fi].extra[e]);
-            }
+            for (int e = 0; e < S::NEX; ++e) bad |= !__builtin_isfinite(ka->f[fi].extra[e]);
         }
         // scale by the largest component first so that tiny or huge normals
         // normalise without underflow or overflow
@@ -341,9 +320,8 @@ void k_query(const QueryArgs a)
         // the FP16 query takes its cell coordinates in FP32
         constexpr bool F32C = P == NIV_FP16;
         // the FP32 and BF16 queries overlap the levels' gathers; the FP16
-        // query and the training forward go level by level (measured faster:
-        // paired dense loads, and the training kernel's registers)
-        constexpr bool PIPE = !F32C && !TRAIN && S::F == 2;
+        // query goes level by level (measured faster: paired dense loads)
+        constexpr bool PIPE = !F32C && S::F == 2;
         if constexpr (S::L > 0 && PIPE) {
             // grid levels for every lane (lanes without work encode the box
             // corner and store zeros), so that the gathers are not inside a
@@ -509,11 +487,6 @@ void k_query(const QueryArgs a)
                 }
             }
         }
-        if constexpr (TRAIN) {
-            uint8_t *xs = a.x_save + chunk * CHUNK_BYTES;
-#pragma unroll
-            for (int k = 0; k < S::DIN; ++k) reinterpret_cast<uint32_t *>(xs)[k * 64 + lane] = row[k];
-        }
         if constexpr (PROBE) {
             uint32_t xo = 0u;
 #pragma unroll
@@ -633,27 +606,6 @@ void k_query(const QueryArgs a)
                             bh[t][4 * ob + 2] = Prec<P>::relu(acc[t][ob].z);
                             bh[t][4 * ob + 3] = Prec<P>::relu(acc[t][ob].w);
                         }
-                    if constexpr (TRAIN) {
-                        uint32_t *xs = reinterpret_cast<uint32_t *>(a.x_save + chunk * CHUNK_BYTES) +
-                                       (S::DIN + (layer - 1) * S::W) * 64;
-                        uint32_t mk[S::W / 32];
-#pragma unroll
-                        for (int d = 0; d < S::W / 32; ++d) mk[d] = 0u;
-#pragma unroll
-                        for (int t = 0; t < TB; ++t)
-#pragma unroll
-                            for (int ob = 0; ob < S::NOB; ++ob)
-#pragma unroll
-                                for (int r = 0; r < 4; ++r) {
-                                    const float v = bh[t][4 * ob + r];
-                                    xs[(16 * ob + 4 * g + r) * 64 + 16 * t + j] = f2u(v);
-                                    const int bit = (t * S::NOB + ob) * 4 + r;
-                                    mk[bit >> 5] |= (v > 0.f ? 1u : 0u) << (bit & 31);
-                                }
-#pragma unroll
-                        for (int d = 0; d < S::W / 32; ++d)
-                            a.mask_save[((chunk * S::H + (layer - 1)) * (S::W / 32) + d) * 64 + lane] = mk[d];
-                    }
                     if (last) {
 #pragma unroll
                         for (int t = 0; t < TB; ++t)
@@ -777,32 +729,6 @@ void k_query(const QueryArgs a)
                 ch[c] = g == 0 ? e[0] : g == 1 ? e[1] : g == 2 ? e[2] : e[3];
             }
             acc_out = (f4){ch[0], ch[1], ch[2], 0.f};
-        }
-        if constexpr (TRAIN) {
-            // Eq. 3: (E - y)^2 / (sg(E^2) + eps); d/dE = 2 (E - y) / (E^2 + eps)
-            float lsum = 0.0f;
-            bool nonfinite = false;
-            if (live) {
-                const float Ev[3] = {acc_out.x, acc_out.y, acc_out.z};
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    float d = 0.0f;
-                    if (work) {
-                        const float r = Ev[c] - a.target[3 * q + c];
-                        const float den = Ev[c] * Ev[c] + a.loss_eps;
-                        d = 2.0f * r / den;
-                        lsum += r * r / den;
-                        nonfinite |= !__builtin_isfinite(d);
-                    }
-                    a.dE[3 * q + c] = d;
-                }
-            }
-            // a diverged output or a non-finite target marks the whole step
-            if (__ballot(nonfinite) != 0ull && lane == 0) atomicOr(a.train_status + 2, 1u);
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off);
-            if (lane == 0) atomicAdd(a.loss, lsum * a.loss_scale);
-            continue;
         }
         float *f_E = ka->f[fi].out_E, *f_L = ka->f[fi].out_L;
         uint8_t *f_flags = ka->f[fi].out_flags;

@@ -3,27 +3,23 @@
 // encoding gradient into the hash grid, and Adam.
 //
 // A step runs these stages on the caller's stream:
-//   1. FP16: k_train_encode writes the samples' input vectors, and
-//      k_train_mlp takes 64 samples at a time forward, through the loss
-//      (Eq. 3, stop-gradient denominator) and backward without leaving
-//      registers and LDS: the weight gradients dW_k = G_{k+1} X_k^T and the
-//      input gradients W_k^T G_{k+1}, all on MFMA;
-//      FP32 (its activations do not fit a wave's registers): the fused query
-//      kernel in training mode saves every layer's input (per 64-sample
-//      chunk, [neuron][sample]) and the ReLU masks and writes d loss / dE,
-//      and k_train_bwd walks back through them (the gradient is transposed
-//      through LDS for dW);
-//   2. in both, pre-permuted transposed weights make the input gradients come
-//      out in the lane layout of the forward activations; each wave keeps
-//      its weight gradient in the matrix-core accumulators over its chunks,
-//      a workgroup's four waves add theirs in LDS and write one row, and
-//      k_dw_sum adds the rows; the gradient of each sample's grid features
-//      is written out level-major per chunk;
+//   1. k_train_encode writes the samples' input vectors;
+//   2. k_train_mlp (FP16) or k_train_net32 (FP32) takes 64 samples at a time
+//      forward, through the loss (Eq. 3, stop-gradient denominator) and
+//      backward without leaving registers and LDS: the weight gradients
+//      dW_k = G_{k+1} X_k^T and the input gradients W_k^T G_{k+1}, all on
+//      MFMA.  FP16: a wave takes a chunk alone, its activations in registers
+//      and its weight gradient in the matrix-core accumulators over its
+//      chunks.  FP32: sixteen waves share a chunk, activations in LDS, each
+//      wave a tile of every weight gradient.  A workgroup writes its weight
+//      gradient as a row (no atomics) and k_dw_sum adds the rows; the
+//      gradient of each sample's grid features is written out level-major
+//      per chunk;
 //   3. the scatter of those feature gradients to the 8 corners of every
 //      level, without global atomics (device-scope atomics execute at the
 //      memory side of this part, ~22 G/s): the contributions are counted
 //      per bin of 4096 grid entries and workgroup (k_grid_count, on a
-//      second stream beside stage 1: it needs only the batch), the
+//      second stream beside stages 1 and 2: it needs only the batch), the
 //      counts are scanned (k_grid_scan_bins; the bins' totals at the start
 //      of the write pass), the contributions are written bin by bin
 //      (k_grid_write), and one or more workgroups per bin sum them in LDS
@@ -135,7 +131,7 @@ __global__ void k_prepare_bwd(const float *__restrict__ params, uint8_t *__restr
     const int tid = blockIdx.x * blockDim.x + threadIdx.x;
     if (tid < n_status) status[tid] = 0u;
     if (tid == 0) *loss = 0.0f;
-    if (tid >= B::N_OPS * 64) return;
+    if (P == NIV_FP32 || tid >= B::N_OPS * 64) return;   // FP32: its network reads the forward's operands
     const int op = tid / 64, lane = tid % 64;
     int64_t off;
     int ne;
@@ -154,22 +150,7 @@ __global__ void k_prepare_bwd(const float *__restrict__ params, uint8_t *__restr
     }
 }
 
-// ---------------------------------------------------------------- backward
-struct BwdArgs {
-    const uint8_t *bwd;        // backward operands
-    const uint8_t *x_save;
-    const uint32_t *mask_save;
-    const float *dE;           // [n][3], without the 1/(3n) factor
-    const float *x;            // [n][3] sample positions
-    float *dw_part;            // [workgroup][weights] each workgroup's weight gradient
-    float *dx0;                // [chunk][L][64] float pairs: gradient of each sample's grid features
-    uint8_t *sflag;            // [n] 1: the sample's features scatter into the grid
-    uint32_t *vmax;            // step word [0]: largest |feature gradient| x loss_scale of a
-                               // scattering sample (float bits; bounds every contribution)
-    int64_t n;
-    float loss_scale;
-};
-
+// ---------------------------------------------------------------- shared parts
 template <int P> struct Mm;
 template <> struct Mm<NIV_FP16> {
     __device__ static u4 h8(const float *v) {
@@ -252,191 +233,7 @@ __device__ inline uint32_t keep2(uint32_t w, uint32_t m)
     return __builtin_bit_cast(uint32_t, (us2)(__builtin_bit_cast(us2, w) * __builtin_bit_cast(us2, m)));
 }
 
-template <class S>
-__global__ __launch_bounds__(256) void k_train_bwd(const BwdArgs a)
-{
-    constexpr int P = NIV_FP32;
-    using B = Bwd<P, S>;
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int g = lane >> 4, j = lane & 15;
-    uint8_t *wbuf = smem + wave * B::WB_BYTES;
-    float *debuf = reinterpret_cast<float *>(wbuf + (B::GB_BYTES > B::DX_BYTES ? B::GB_BYTES : B::DX_BYTES));
-    // the wave's weight gradient, summed over its chunks in the matrix-core
-    // accumulators (no LDS atomics per chunk)
-    f4 dwacc[B::N_TILES];
-#pragma unroll
-    for (int t = 0; t < B::N_TILES; ++t) dwacc[t] = (f4){0.f, 0.f, 0.f, 0.f};
-
-    const int64_t n_chunks = (a.n + 63) / 64;
-    const int64_t n_waves = (int64_t)gridDim.x * 4;
-    float gmax = 0.0f;   // largest |feature gradient| of this lane's scattering samples
-    for (int64_t chunk = (int64_t)blockIdx.x * 4 + wave; chunk < n_chunks; chunk += n_waves) {
-        const int64_t q = chunk * 64 + lane;
-        const bool live = q < a.n;
-        float dEl[3] = {0.f, 0.f, 0.f};
-        if (live) {
-            dEl[0] = a.dE[3 * q]; dEl[1] = a.dE[3 * q + 1]; dEl[2] = a.dE[3 * q + 2];
-        }
-#pragma unroll
-        for (int c = 0; c < 3; ++c) debuf[c * 64 + lane] = dEl[c];
-        wave_lds_fence();
-        const uint8_t *xs = a.x_save + chunk * B::CHUNK_BYTES;
-        const uint8_t *bw = a.bwd;
-
-        // ---- output layer: dW_H[c][n] = sum_px dE[px][c] X_H[n][px]
-        // (the X_H operands are loaded together first: one memory latency)
-        {
-            const int xrow = S::DIN + (S::H - 1) * S::W;
-            const float *xf = reinterpret_cast<const float *>(xs);
-            float xv[S::W / 16][16];
-#pragma unroll
-            for (int nb = 0; nb < S::W / 16; ++nb)
-#pragma unroll
-                for (int s = 0; s < 16; ++s) xv[nb][s] = xf[(xrow + 16 * nb + j) * 64 + 4 * s + g];
-#pragma unroll
-            for (int nb = 0; nb < S::W / 16; ++nb) {
-                f4 acc = dwacc[nb];
-#pragma unroll
-                for (int s = 0; s < 16; ++s) {
-                    const float av = j < 3 ? debuf[j * 64 + 4 * s + g] : 0.f;
-                    acc = Prec<NIV_FP32>::mma1(av, xv[nb][s], acc);
-                }
-                dwacc[nb] = acc;
-            }
-        }
-        // ---- gradient w.r.t. x_H = W_H^T dE, lane layout of the forward
-        f4 G[4][B::NOB];
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int ib = 0; ib < B::NIB; ++ib) {
-                const f4 z = {0.f, 0.f, 0.f, 0.f};
-                const float av = reinterpret_cast<const float *>(bw + ib * B::OUT_OP)[lane];
-                const float bv = g < 3 ? debuf[g * 64 + 16 * t + j] : 0.f;
-                G[t][ib] = Prec<NIV_FP32>::mma1(av, bv, z);
-            }
-        // ---- hidden layers k = H-1 .. 0
-#pragma unroll
-        for (int k = S::H - 1; k >= 0; --k) {
-            // G is d loss / d x_{k+1}; through the ReLU: x_{k+1} > 0
-            uint32_t mk[S::W / 32];
-#pragma unroll
-            for (int d = 0; d < S::W / 32; ++d)
-                mk[d] = a.mask_save[((chunk * S::H + k) * (S::W / 32) + d) * 64 + lane];
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int ob = 0; ob < B::NOB; ++ob) {
-                    const int b0 = (t * B::NOB + ob) * 4;
-                    if (!((mk[(b0 + 0) >> 5] >> ((b0 + 0) & 31)) & 1u)) G[t][ob].x = 0.f;
-                    if (!((mk[(b0 + 1) >> 5] >> ((b0 + 1) & 31)) & 1u)) G[t][ob].y = 0.f;
-                    if (!((mk[(b0 + 2) >> 5] >> ((b0 + 2) & 31)) & 1u)) G[t][ob].z = 0.f;
-                    if (!((mk[(b0 + 3) >> 5] >> ((b0 + 3) & 31)) & 1u)) G[t][ob].w = 0.f;
-                }
-            // transpose G through LDS: [neuron][64 samples]
-            float *gb = reinterpret_cast<float *>(wbuf);
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int ob = 0; ob < B::NOB; ++ob) {
-                    gb[(16 * ob + 4 * g + 0) * 64 + 16 * t + j] = G[t][ob].x;
-                    gb[(16 * ob + 4 * g + 1) * 64 + 16 * t + j] = G[t][ob].y;
-                    gb[(16 * ob + 4 * g + 2) * 64 + 16 * t + j] = G[t][ob].z;
-                    gb[(16 * ob + 4 * g + 3) * 64 + 16 * t + j] = G[t][ob].w;
-                }
-            wave_lds_fence();
-            // dW_k += G X_k^T over the chunk's 64 samples; the X_k operands do
-            // not depend on the output block and are loaded together first
-            constexpr int DK_MAX = S::DIN > S::W ? S::DIN : S::W;
-            const int dk = (k == 0) ? S::DIN : S::W;
-            const int xrow = (k == 0) ? 0 : S::DIN + (k - 1) * S::W;
-            const int tb = B::tile_base(k);   // this layer's tiles: ob * (dk / 16) + ib
-            const float *xf = reinterpret_cast<const float *>(xs);
-            float xv[DK_MAX / 16][16];
-#pragma unroll
-            for (int ib = 0; ib < DK_MAX / 16; ++ib)
-#pragma unroll
-                for (int s = 0; s < 16; ++s)
-                    xv[ib][s] = ib * 16 < dk ? xf[(int64_t)(xrow + 16 * ib + j) * 64 + 4 * s + g] : 0.f;
-#pragma unroll
-            for (int ob = 0; ob < B::NOB; ++ob)
-#pragma unroll
-                for (int ib = 0; ib < DK_MAX / 16; ++ib) {
-                    if (ib * 16 >= dk) break;
-                    f4 acc = dwacc[tb + ob * (dk / 16) + ib];
-#pragma unroll
-                    for (int s = 0; s < 16; ++s)
-                        acc = Prec<NIV_FP32>::mma1(gb[(16 * ob + j) * 64 + 4 * s + g], xv[ib][s], acc);
-                    dwacc[tb + ob * (dk / 16) + ib] = acc;
-                }
-            // d loss / d x_k = W_k^T G (grid rows only for k = 0)
-            const int nib = (k == 0) ? B::GIB : B::NIB;
-            const uint8_t *bk = (k == 0) ? bw + B::OUT_BYTES + (S::H - 1) * B::HID_BYTES
-                                         : bw + B::OUT_BYTES + (k - 1) * B::HID_BYTES;
-            f4 Gn[4][B::NOB];
-#pragma unroll
-            for (int ib = 0; ib < B::NIB; ++ib) {
-                if (ib >= nib) break;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) Gn[t][ib] = (f4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int c = 0; c < B::HOPS; ++c) {
-                    const float av = reinterpret_cast<const float *>(bk + (ib * B::HOPS + c) * B::OPB)[lane];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const f4 gv = G[t][c / 4];
-                        const float bv = (c % 4 == 0) ? gv.x : (c % 4 == 1) ? gv.y : (c % 4 == 2) ? gv.z : gv.w;
-                        Gn[t][ib] = Prec<NIV_FP32>::mma1(av, bv, Gn[t][ib]);
-                    }
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int ob = 0; ob < B::NOB; ++ob) G[t][ob] = Gn[t][ob];
-        }
-        // ---- grid-feature gradients: rows 16ib + 4g + r of sample 16t + j,
-        // through LDS ([sample][2L], rows padded by two floats so that a
-        // level's column spreads over the banks), out as [chunk][level][64]
-        // float pairs (one coalesced store per level)
-        {
-            float *dx = reinterpret_cast<float *>(wbuf);
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int ib = 0; ib < B::GIB; ++ib) {
-                    float *d = dx + (16 * t + j) * B::NFP + 16 * ib + 4 * g;
-                    d[0] = G[t][ib].x; d[1] = G[t][ib].y; d[2] = G[t][ib].z; d[3] = G[t][ib].w;
-                }
-            wave_lds_fence();
-            // a sample scatters when its dE is finite and not zero (a non-finite
-            // dE marks the step non-finite in the forward and never reaches the grid)
-            bool scatter = live && (dEl[0] != 0.f || dEl[1] != 0.f || dEl[2] != 0.f) &&
-                           __builtin_isfinite(dEl[0]) && __builtin_isfinite(dEl[1]) &&
-                           __builtin_isfinite(dEl[2]);
-            if (scatter) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) scatter &= __builtin_isfinite(a.x[3 * q + c]);
-            }
-            if (live) {
-                const float2 *mine = reinterpret_cast<const float2 *>(dx + lane * B::NFP);
-                float2 *dst = reinterpret_cast<float2 *>(a.dx0) + chunk * 64 * S::L + lane;
-#pragma unroll
-                for (int l = 0; l < S::L; ++l) {
-                    const float2 v = mine[l];
-                    dst[l * 64] = v;
-                    if (scatter) gmax = fmaxf(gmax, fmaxf(fabsf(v.x), fabsf(v.y)));
-                }
-                a.sflag[q] = scatter ? 1 : 0;
-            }
-        }
-    }
-    grad_bound(gmax, a.loss_scale, a.vmax, lane);
-    store_weight_gradient<P, S>(dwacc, smem, a.dw_part, wave, g, j);
-}
-
-// ---------------------------------------------------------------- FP16: encoding
+// ---------------------------------------------------------------- encoding
 // The input vectors of a batch.  A sample's 128 latents lie at random in a
 // 7 MB table, so the pass is bound by the rate of cache lines from L2.  The
 // levels are dealt to the XCDs, two each, so that a 4 MB L2 holds its levels
@@ -444,35 +241,35 @@ __global__ __launch_bounds__(256) void k_train_bwd(const BwdArgs a)
 // every XCD taking every level, one pair after the other.  Encoding inside
 // the forward's kernel (two waves per SIMD beside its weights) took 135 us
 // for both.  The count pass beside it costs nothing (83 us without it).
-// Input dword k (columns 2k, 2k + 1) of sample q of a chunk goes to
-// x_pair[chunk][k][q], and column c to x_row[chunk][c][q]: the forward reads
-// the pairs, the weight gradient the rows.
+// Column c of sample q of a chunk goes to x_row[chunk][c][q]; FP16: also dword
+// k (columns 2k, 2k + 1) to x_pair[chunk][k][q], the forward's operand (the
+// weight gradient reads the rows).
 struct EncodeArgs {
     const float *x, *nrm, *extra;   // [n][3], [n][3], [n][n_extra]
     const uint8_t *valid;           // [n] or null
     const uint8_t *model;           // prepared model (level table first)
     uint64_t grid_off;
     uint32_t grid_bytes, hash_mask;
-    uint32_t *x_pair;
-    uint16_t *x_row;
+    uint32_t *x_pair;               // FP16
+    void *x_row;                    // halves or floats
     int64_t n;
     double lo[3], hi[3];
 };
 
 constexpr int kEncWaves = 4;
 
-template <class S>
+template <int P, class S>
 __global__ __launch_bounds__(64 * kEncWaves) void k_train_encode(const EncodeArgs a)
 {
     typedef const __attribute__((address_space(4))) LevelConst *ConstLevels;
-    constexpr int P = NIV_FP16;
     constexpr int PER = (S::L + kXcds - 1) / kXcds;   // levels of an XCD
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int xcd = blockIdx.x % kXcds;
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void *)(a.model + a.grid_off), (short)0, (int)a.grid_bytes, 0x00020000);
     ConstLevels lvs = (ConstLevels)a.model;
-    static_assert(S::GF / 2 + 8 + 8 * S::NEX == S::DIN / 2, "grid, normal and scene columns fill the rows");
+    static_assert(S::GF / 2 + 8 + 8 * S::NEX == S::DIN / 2 && S::DIN == S::DIN_IN,
+                  "grid, normal and scene columns fill the rows, in the parameters' order");
     static_assert(S::H * S::W >= S::DIN, "both copies of the inputs fit the chunk's saved rows");
     const int64_t chunk = (int64_t)(blockIdx.x / kXcds) * kEncWaves + wave;
     if (chunk * 64 >= a.n) return;
@@ -495,13 +292,18 @@ __global__ __launch_bounds__(64 * kEncWaves) void k_train_encode(const EncodeArg
     }
     const float nm = fmaxf(fabsf(v[3]), fmaxf(fabsf(v[4]), fabsf(v[5])));
     work = work && nm > 0.0f;
-    uint32_t *pair = a.x_pair + chunk * (S::DIN / 2) * 64 + lane;
-    uint16_t *row = a.x_row + chunk * S::DIN * 64 + lane;
-    auto put = [&](int k, uint32_t w) {   // no bias anywhere: a sample without work feeds zeros
-        w = work ? w : 0u;
-        pair[k * 64] = w;
-        row[(2 * k) * 64] = (uint16_t)w;
-        row[(2 * k + 1) * 64] = (uint16_t)(w >> 16);
+    auto put = [&](int k, float u, float w) {   // no bias anywhere: a sample without work feeds zeros
+        if constexpr (P == NIV_FP32) {
+            float *row = reinterpret_cast<float *>(a.x_row) + (chunk * S::DIN + 2 * k) * 64 + lane;
+            row[0] = work ? u : 0.0f;
+            row[64] = work ? w : 0.0f;
+        } else {
+            const uint32_t h = work ? Prec<P>::pack(u, w) : 0u;
+            a.x_pair[(chunk * (S::DIN / 2) + k) * 64 + lane] = h;
+            uint16_t *row = reinterpret_cast<uint16_t *>(a.x_row) + (chunk * S::DIN + 2 * k) * 64 + lane;
+            row[0] = (uint16_t)h;
+            row[64] = (uint16_t)(h >> 16);
+        }
     };
     double p[3];
 #pragma unroll
@@ -523,13 +325,13 @@ __global__ __launch_bounds__(64 * kEncWaves) void k_train_encode(const EncodeArg
         float sh[16];
         sh16(nx * rn, ny * rn, nz * rn, sh);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) put(S::GF / 2 + k, Prec<P>::pack(sh[2 * k], sh[2 * k + 1]));
+        for (int k = 0; k < 8; ++k) put(S::GF / 2 + k, sh[2 * k], sh[2 * k + 1]);
 #pragma unroll
         for (int e = 0; e < S::NEX; ++e)
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const float t = te[e] * (float)(1 << k);
-                put(S::GF / 2 + 8 + 8 * e + k, Prec<P>::pack(sinpif(t), cospif(t)));
+                put(S::GF / 2 + 8 + 8 * e + k, sinpif(t), cospif(t));
             }
     }
 #pragma unroll
@@ -537,7 +339,7 @@ __global__ __launch_bounds__(64 * kEncWaves) void k_train_encode(const EncodeArg
         const int l = i == 0 ? xcd : S::L - 1 - xcd;
         if (l >= S::L) continue;
         const f2 r = level_blend<P>(f[i]);
-        put(l, Prec<P>::pack(r.x, r.y));
+        put(l, r.x, r.y);
     }
 }
 
@@ -886,10 +688,279 @@ __global__ __launch_bounds__(256) void k_train_mlp(const MlpArgs a)
     store_weight_gradient<P, S>(dwacc, smem, a.dw_part, wave, g, j);
 }
 
+// ---------------------------------------------------------------- FP32: network
+// Forward, loss and backward of 64 samples at a time by sixteen waves, every
+// layer's input and gradient in LDS ([neuron][sample], rows padded by four so
+// that neither the row-wise nor the column-wise operand reads collide).  Wave
+// (t, b) makes the 16 x 16 block of samples 16 t and neurons 16 b of each
+// layer and, transposed, tile (t, b) of each weight gradient: a wave carries
+// H + 1 accumulator tiles instead of the 52 of a wave that takes a chunk
+// alone (900 bytes of scratch there).  The transposed weights of the backward
+// are read from the forward's operands; the gradient of x_k takes the place
+// of x_{k+1}.  Bound by the FP32 matrix rate (7.3 us a chunk and CU) and the
+// 2 H + 3 barriers around it: room network, 2^18 samples, 225 us and the
+// encoding 92 us, where a forward that saved its activations took 220 us and
+// a wave-per-chunk backward 451 us; 20011 samples: 52 + 115 us -> 43 + 11 us.
+//
+// Order of the weight gradient's sums: chunks c, c + n_streams, ... make a
+// stream; a workgroup adds its streams, and k_dw_sum the workgroups.
+template <class S> struct Net32 {
+    using O = Ops<NIV_FP32, S>;
+    static constexpr int RS = 68;                              // floats of a row of 64 samples
+    static constexpr int X_OFF = O::W_BYTES / 4;               // X_0, then X_1 .. X_H
+    static constexpr int G_OFF = X_OFF + (S::DIN + S::H * S::W) * RS;
+    static constexpr int DE_OFF = G_OFF + S::W * RS;           // [3][64]
+    static constexpr int FLAG_OFF = DE_OFF + 3 * 64;           // [64] 1: scatters
+    static constexpr int LDS_BYTES = (FLAG_OFF + 64) * 4;
+    static_assert(LDS_BYTES <= 160 * 1024, "workgroup LDS");
+    static_assert(S::W == 64 && S::DIN <= 64, "sixteen waves take four blocks of neurons by four of samples");
+    static_assert(2 * S::L <= S::DIN, "grid columns first");
+    __device__ static constexpr int x_off(int k) { return X_OFF + (k == 0 ? 0 : S::DIN + (k - 1) * S::W) * RS; }
+};
+
+struct Net32Args {
+    const uint8_t *fwd;             // operand block of the prepared model
+    const float *x_row;             // [chunk][DIN][64] the batch's inputs, see k_train_encode
+    const float *x, *nrm, *extra, *target;
+    const uint8_t *valid;
+    float *dw_part;                 // [workgroup][weights]
+    float *dx0;                     // [chunk][L][64] float pairs
+    uint8_t *sflag;                 // [n] 1: the sample's features scatter into the grid
+    uint32_t *status;               // step words: [0] bound on the contributions, [2] not finite
+    float *loss;
+    int64_t n;
+    int64_t n_streams;
+    int32_t wg_streams;             // streams of a workgroup: 1 or 2 (a row of weight gradients for
+                                    // each) or 4 (one row for their sum)
+    float loss_scale, loss_eps;
+};
+
+template <class S>
+__global__ __launch_bounds__(1024) void k_train_net32(const Net32Args a)
+{
+    using N = Net32<S>;
+    using O = Ops<NIV_FP32, S>;
+    using B = Bwd<NIV_FP32, S>;
+    constexpr int RS = N::RS, KL = S::KLG;
+    extern __shared__ __attribute__((aligned(16))) float sm[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, j = lane & 15;
+    const int t = wave & 3, b = wave >> 2;   // block of samples (weight gradients: of rows), of neurons (columns)
+    for (int k = tid; k < O::W_BYTES / 16; k += 1024)
+        reinterpret_cast<u4 *>(sm)[k] = reinterpret_cast<const u4 *>(a.fwd)[k];
+    const float *wl0 = sm, *wout = sm + (O::L0_BYTES + (S::H - 1) * O::HID_BYTES) / 4;
+    auto whid = [&](int k) { return sm + (O::L0_BYTES + (k - 1) * O::HID_BYTES) / 4; };   // W_k, k = 1 .. H-1
+    float *gbuf = sm + N::G_OFF, *debuf = sm + N::DE_OFF;
+    uint32_t *flags = reinterpret_cast<uint32_t *>(sm + N::FLAG_OFF);
+    const f4 z = {0.f, 0.f, 0.f, 0.f};
+    f4 acc[S::H + 1], tot[S::H + 1];   // weight gradients of layers 0 .. H: of the stream, of the workgroup
+#pragma unroll
+    for (int k = 0; k <= S::H; ++k) acc[k] = tot[k] = z;
+    float gmax = 0.0f, lsum = 0.0f;
+    bool bad = false;
+    const int64_t n_chunks = (a.n + 63) / 64;
+    const int64_t first = (int64_t)blockIdx.x * a.wg_streams;
+    const bool apart = a.wg_streams < 4;
+    // a row of weight gradients: tile (t, b) of each layer
+    auto store_row = [&](int64_t r, const f4 (&v)[S::H + 1]) {
+        float *row = a.dw_part + r * B::NMLP;
+#pragma unroll
+        for (int k = 0; k < S::H; ++k) {
+            const int dk = k == 0 ? S::DIN : S::W;
+            if (16 * b >= dk) continue;
+            float *dst = row + (k == 0 ? 0 : S::W * S::DIN + (k - 1) * S::W * S::W) + (16 * t + 4 * g) * dk + 16 * b + j;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) dst[i * dk] = v[k][i];
+        }
+        if (b == 3 && g == 0) {
+            float *dst = row + S::W * S::DIN + (S::H - 1) * S::W * S::W + 16 * t + j;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) dst[i * S::W] = v[S::H][i];
+        }
+    };
+    // transposed operands: W_k[16 (c / 4) + 4 g + c % 4][16 b + j] in the forward's block
+    const int thid = (4 * b + (j & 3)) * 64 + 16 * (j >> 2) + 4 * g;
+    const int tout = (4 * b + (j & 3)) * 64 + 16 * (j >> 2) + g;
+    const int tl0 = ((16 * b + j) % KL) * 64 + 16 * ((16 * b + j) / KL) + 4 * g;
+    // row and quad of samples that this thread brings in
+    const int xr = tid >> 4, xq = (tid & 15) * 4;
+    int st = 0;
+    int64_t chunk = first;
+    f4 xin = z;
+    if (chunk < n_chunks && xr < S::DIN) xin = *reinterpret_cast<const f4 *>(a.x_row + (chunk * S::DIN + xr) * 64 + xq);
+    while (chunk < n_chunks) {
+        if (xr < S::DIN) *reinterpret_cast<f4 *>(sm + N::x_off(0) + xr * RS + xq) = xin;
+        // the chunk after this one: of the stream, else of the next stream
+        int64_t next = chunk + a.n_streams;
+        bool fold = false;
+        if (next >= n_chunks) {
+            fold = true;
+            ++st;
+            next = st < a.wg_streams ? first + st : n_chunks;
+        }
+        if (next < n_chunks && xr < S::DIN)
+            xin = *reinterpret_cast<const f4 *>(a.x_row + (next * S::DIN + xr) * 64 + xq);
+        // the sample of waves 0 .. 3, lanes 0 .. 15: does it count, its target
+        const int64_t q = chunk * 64 + 16 * t + j;
+        bool work = false, pos_ok = false;
+        float y[3] = {0.f, 0.f, 0.f};
+        if (b == 0 && g == 0 && q < a.n) {
+            work = !a.valid || a.valid[q] != 0;
+            pos_ok = true;
+            float nm = 0.0f;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const float xv = a.x[3 * q + c], nv = a.nrm[3 * q + c];
+                pos_ok = pos_ok && __builtin_isfinite(xv);
+                work = work && __builtin_isfinite(nv);
+                nm = fmaxf(nm, fabsf(nv));
+                y[c] = a.target[3 * q + c];
+            }
+            work = work && pos_ok && nm > 0.0f;
+#pragma unroll
+            for (int e = 0; e < S::NEX; ++e) work = work && __builtin_isfinite(a.extra[q * S::NEX + e]);
+        }
+        __syncthreads();
+        // ---- forward
+#pragma unroll
+        for (int k = 0; k < S::H; ++k) {
+            const float *src = sm + N::x_off(k) + 16 * t + j;
+            f4 v = z;
+            if (k == 0) {
+                const float *w = wl0 + b * (O::L0_OB / 4) + lane;
+#pragma unroll
+                for (int c = 0; c < KL; ++c) v = Prec<NIV_FP32>::mma1(w[c * 64], src[(KL * g + c) * RS], v);
+            } else {
+                const float *w = whid(k) + b * (O::HROW / 4) + lane;
+#pragma unroll
+                for (int c = 0; c < S::W / 4; ++c)
+                    v = Prec<NIV_FP32>::mma1(w[c * 64], src[(16 * (c / 4) + 4 * g + c % 4) * RS], v);
+            }
+            float *dst = sm + N::x_off(k + 1) + (16 * b + 4 * g) * RS + 16 * t + j;
+            dst[0] = Prec<NIV_FP32>::relu(v.x);
+            dst[RS] = Prec<NIV_FP32>::relu(v.y);
+            dst[2 * RS] = Prec<NIV_FP32>::relu(v.z);
+            dst[3 * RS] = Prec<NIV_FP32>::relu(v.w);
+            __syncthreads();
+        }
+        // ---- output, loss (Eq. 3) and d loss / dE
+        if (b == 0) {
+            const float *src = sm + N::x_off(S::H) + 16 * t + j, *w = wout + lane;
+            f4 v = z;
+#pragma unroll
+            for (int c = 0; c < S::W / 4; ++c)
+                v = Prec<NIV_FP32>::mma1(w[c * 64], src[(16 * (c / 4) + 4 * g + c % 4) * RS], v);
+            if (g == 0) {
+                const float E[3] = {v.x, v.y, v.z};
+                bool scatter = false, finite = true;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    float d = 0.0f;
+                    if (work) {
+                        const float r = E[c] - y[c], den = E[c] * E[c] + a.loss_eps;
+                        d = 2.0f * r / den;
+                        lsum += r * r / den;
+                        bad |= !__builtin_isfinite(d);
+                    }
+                    debuf[c * 64 + 16 * t + j] = d;
+                    scatter |= d != 0.0f;
+                    finite = finite && __builtin_isfinite(d);
+                }
+                scatter = scatter && finite && pos_ok;
+                flags[16 * t + j] = scatter ? 1u : 0u;
+                if (q < a.n) a.sflag[q] = scatter ? 1 : 0;
+            }
+        }
+        __syncthreads();
+        // ---- backward: dW_H = dE X_H^T, and the gradient of x_H through its ReLU
+        if (b == 3) {
+            const float *xk = sm + N::x_off(S::H) + (16 * t + j) * RS + g;
+#pragma unroll
+            for (int s = 0; s < 16; ++s)
+                acc[S::H] = Prec<NIV_FP32>::mma1(j < 3 ? debuf[j * 64 + 4 * s + g] : 0.f, xk[4 * s], acc[S::H]);
+        }
+        {
+            const f4 v = Prec<NIV_FP32>::mma1(wout[tout], g < 3 ? debuf[g * 64 + 16 * t + j] : 0.f, z);
+            const float *xk = sm + N::x_off(S::H) + (16 * b + 4 * g) * RS + 16 * t + j;
+            float *dst = gbuf + (16 * b + 4 * g) * RS + 16 * t + j;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dst[r * RS] = xk[r * RS] > 0.f ? v[r] : 0.f;
+        }
+        __syncthreads();
+        // ---- layers k = H-1 .. 1: dW_k = G_{k+1} X_k^T and the gradient of x_k
+#pragma unroll
+        for (int k = S::H - 1; k >= 1; --k) {
+            const float *gs = k == S::H - 1 ? gbuf : sm + N::x_off(k + 2);
+            const float *xs = sm + N::x_off(k);
+            {
+                const float *ga = gs + (16 * t + j) * RS + g, *xb = xs + (16 * b + j) * RS + g;
+#pragma unroll
+                for (int s = 0; s < 16; ++s) acc[k] = Prec<NIV_FP32>::mma1(ga[4 * s], xb[4 * s], acc[k]);
+            }
+            f4 v = z;
+            const float *w = whid(k) + thid, *gv = gs + 4 * g * RS + 16 * t + j;
+#pragma unroll
+            for (int c = 0; c < S::W / 4; ++c)
+                v = Prec<NIV_FP32>::mma1(w[(c / 4) * (O::HROW / 4) + c % 4], gv[(16 * (c / 4) + c % 4) * RS], v);
+            const float *xk = xs + (16 * b + 4 * g) * RS + 16 * t + j;
+            float *dst = sm + N::x_off(k + 1) + (16 * b + 4 * g) * RS + 16 * t + j;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dst[r * RS] = xk[r * RS] > 0.f ? v[r] : 0.f;
+            __syncthreads();
+        }
+        // ---- dW_0 and the gradient of the grid features
+        {
+            const float *gs = S::H == 1 ? gbuf : sm + N::x_off(2);
+            if (b < S::DIN / 16) {
+                const float *ga = gs + (16 * t + j) * RS + g, *xb = sm + N::x_off(0) + (16 * b + j) * RS + g;
+#pragma unroll
+                for (int s = 0; s < 16; ++s) acc[0] = Prec<NIV_FP32>::mma1(ga[4 * s], xb[4 * s], acc[0]);
+            }
+            if (b < B::GIB) {
+                f4 v = z;
+                const float *w = wl0 + tl0, *gv = gs + 4 * g * RS + 16 * t + j;
+#pragma unroll
+                for (int c = 0; c < S::W / 4; ++c)
+                    v = Prec<NIV_FP32>::mma1(w[(c / 4) * (O::L0_OB / 4) + c % 4], gv[(16 * (c / 4) + c % 4) * RS], v);
+                const int64_t qd = chunk * 64 + 16 * t + j;
+                if (qd < a.n) {
+                    float2 *dst = reinterpret_cast<float2 *>(a.dx0) + (chunk * S::L + 8 * b + 2 * g) * 64 + 16 * t + j;
+                    dst[0] = make_float2(v.x, v.y);
+                    dst[64] = make_float2(v.z, v.w);
+                    if (flags[16 * t + j])
+                        gmax = fmaxf(gmax, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+                }
+            }
+        }
+        if (fold) {
+            if (apart) store_row(first + st - 1, acc);
+#pragma unroll
+            for (int k = 0; k <= S::H; ++k) {
+                tot[k] += acc[k];
+                acc[k] = z;
+            }
+        }
+        chunk = next;
+        __syncthreads();   // the buffers are written again
+    }
+    if (__ballot(bad) != 0ull && lane == 0) atomicOr(a.status + 2, 1u);
+    if (b == 0) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off);
+        if (lane == 0) atomicAdd(a.loss, lsum * a.loss_scale);
+    }
+    grad_bound(gmax, a.loss_scale, a.status, lane);
+    if (!apart) store_row(blockIdx.x, tot);
+    for (; apart && st < a.wg_streams; ++st) store_row(first + st, acc);   // streams without a chunk: zeros
+}
+
 // Column sums of the per-workgroup weight gradients, scaled, into the
 // gradient: a workgroup takes 16 columns; its 16 row groups each add rows
 // g, g + 16, g + 32, ... of a column (eight loads in flight), and the 16
 // partial sums are added in row-group order (a fixed summation order).
+// QUAD: a row is the sum of four rows of the memory, added in their order
+// (streams that were stored apart).
+template <bool QUAD>
 __global__ __launch_bounds__(256) void k_dw_sum(const float *__restrict__ part, int64_t nmlp, int rows,
                                                float *__restrict__ out, float scale)
 {
@@ -897,12 +968,20 @@ __global__ __launch_bounds__(256) void k_dw_sum(const float *__restrict__ part, 
     const int c = threadIdx.x & 15, rg = threadIdx.x >> 4;
     const int64_t k = (int64_t)blockIdx.x * 16 + c;
     float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    auto row = [&](int64_t r) {
+        if constexpr (QUAD) {
+            const float *q = part + 4 * r * nmlp + k;
+            return ((q[0] + q[nmlp]) + q[2 * nmlp]) + q[3 * nmlp];
+        } else {
+            return part[r * nmlp + k];
+        }
+    };
     if (k < nmlp) {
         int r = rg;
         for (; r + 7 * 16 < rows; r += 8 * 16)
 #pragma unroll
-            for (int u = 0; u < 8; ++u) s[u] += part[(int64_t)(r + 16 * u) * nmlp + k];
-        for (; r < rows; r += 16) s[0] += part[(int64_t)r * nmlp + k];
+            for (int u = 0; u < 8; ++u) s[u] += row(r + 16 * u);
+        for (; r < rows; r += 16) s[0] += row(r);
 #pragma unroll
         for (int u = 1; u < 8; ++u) s[0] += s[u];
     }
@@ -922,7 +1001,7 @@ __global__ __launch_bounds__(256) void k_dw_sum(const float *__restrict__ part, 
 constexpr int kBinShift = 12;                 // 4096 entries (32 KB of FP32 pairs) per bin
 constexpr int kBinEntries = 1 << kBinShift;
 constexpr int kMaxBins = 2048;
-constexpr int kBwdMaxBlocks = 512;            // workgroups of the backward (4 dW rows each)
+constexpr int kBwdMaxBlocks = 512;            // rows of weight gradients
 constexpr int kScatterBlocks = 512;           // workgroups of the count and write passes
 constexpr int kAccumRecords = 98304;          // records one accumulating workgroup takes (1.5x a
                                               // hashed level's bin at 2^18 samples: those stay whole)
@@ -1672,37 +1751,11 @@ static hipError_t backward_t(const Model &m, const niv_batch &b, const niv_train
     // captured; every gradient value is stored whole (the grid by the
     // accumulating and merging passes, the MLP by k_dw_sum)
     uint32_t *status = reinterpret_cast<uint32_t *>(ws + L.vmax_off);
-    hipLaunchKernelGGL((k_prepare_bwd<P, S>), dim3((B::N_OPS * 64 + 255) / 256), dim3(256), 0,
+    hipLaunchKernelGGL((k_prepare_bwd<P, S>), dim3(P == NIV_FP32 ? 1 : (B::N_OPS * 64 + 255) / 256), dim3(256), 0,
                        stream, st.params, ws + L.bwd_off, m.n_grid_values, status, kStatusWords,
                        st.loss);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // 1. forward with saves, loss and d loss / dE (non-finite ones mark the step)
-    QueryArgs a;
-    memset(&a, 0, sizeof(a));
-    a.n_frames = 1;
-    a.f[0].pos = b.x;
-    a.f[0].nrm = b.nrm;
-    a.f[0].model = static_cast<const uint8_t *>(st.model);
-    a.f[0].count = b.count;
-    a.f[0].tile_begin = 0;
-    a.grid_off = (uint64_t)op_layout(m.kind, (niv_precision)P).grid_off;
-    a.grid_bytes = (uint32_t)(m.n_grid_values * (P == NIV_FP32 ? 4 : 2));
-    a.hash_mask = (uint32_t)((int64_t(1) << m.cfg.log2_T) - 1);
-    for (int c = 0; c < 3; ++c) {
-        a.lo[c] = m.cfg.aabb_min[c];
-        a.hi[c] = m.cfg.aabb_max[c];
-    }
-    a.extra_ps = b.extra;
-    a.target = b.target;
-    a.valid = b.valid;
-    a.x_save = ws + L.x_off;
-    a.mask_save = reinterpret_cast<uint32_t *>(ws + L.mask_off);
-    a.dE = reinterpret_cast<float *>(ws + L.dE_off);
-    a.loss = st.loss;
-    a.train_status = status;
-    a.loss_scale = (float)(1.0 / (3.0 * (double)b.count));  // used by the forward's loss sum
-    a.loss_eps = 0.01f;
     // grid scatter arguments
     ScatterArgs sa;
     memset(&sa, 0, sizeof(sa));
@@ -1726,9 +1779,12 @@ static hipError_t backward_t(const Model &m, const niv_batch &b, const niv_train
     sa.n_entries = m.n_grid_values / 2;
     sa.n_levels = m.cfg.n_levels;
     sa.n_bins = (int32_t)((sa.n_entries + kBinEntries - 1) >> kBinShift);
-    sa.hash_mask = a.hash_mask;
+    sa.hash_mask = (uint32_t)((int64_t(1) << m.cfg.log2_T) - 1);
     sa.loss_scale = (float)(1.0 / (3.0 * (double)b.count));
-    for (int c = 0; c < 3; ++c) { sa.lo[c] = a.lo[c]; sa.hi[c] = a.hi[c]; }
+    for (int c = 0; c < 3; ++c) {
+        sa.lo[c] = m.cfg.aabb_min[c];
+        sa.hi[c] = m.cfg.aabb_max[c];
+    }
     sa.cstride = (sa.n_bins + 3) & ~3;
     sa.parts_shift = scatter_parts_shift(b.count, sa.n_levels);
     if (sa.n_bins > kMaxBins) return hipErrorInvalidValue;
@@ -1745,85 +1801,94 @@ static hipError_t backward_t(const Model &m, const niv_batch &b, const niv_train
     hipLaunchKernelGGL(k_grid_count, dim3(kScatterBlocks), dim3(kScatterThreads), 0, side, sa);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = hipEventRecord(ev.join, side)) != hipSuccess) return e;
-    // 1./2. forward, loss and backward
+    // 1./2. encoding, forward, loss and backward
     const int64_t n_chunks = (b.count + 63) / 64;
     float *dw_part = reinterpret_cast<float *>(ws + L.dw_off);
-    float *dx0 = reinterpret_cast<float *>(ws + L.dx0_off);
-    int64_t bwd_blocks = 0;   // workgroups that write a row of weight gradients
+    constexpr float loss_eps = 0.01f;
+    EncodeArgs ea;
+    memset(&ea, 0, sizeof(ea));
+    ea.x = b.x;
+    ea.nrm = b.nrm;
+    ea.extra = b.extra;
+    ea.valid = b.valid;
+    ea.model = sa.model;
+    ea.grid_off = (uint64_t)op_layout(m.kind, (niv_precision)P).grid_off;
+    ea.grid_bytes = (uint32_t)(m.n_grid_values * B::ES);
+    ea.hash_mask = sa.hash_mask;
+    ea.x_pair = reinterpret_cast<uint32_t *>(ws + L.x_off);
+    ea.x_row = ws + L.x_off + (P == NIV_FP16 ? n_chunks * S::DIN * 128 : 0);
+    ea.n = b.count;
+    for (int c = 0; c < 3; ++c) { ea.lo[c] = sa.lo[c]; ea.hi[c] = sa.hi[c]; }
+    hipLaunchKernelGGL((k_train_encode<P, S>), dim3((unsigned)(kXcds * ((n_chunks + kEncWaves - 1) / kEncWaves))),
+                       dim3(64 * kEncWaves), 0, stream, ea);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    int64_t rows = 0;     // rows of weight gradients
+    bool quad = false;    // each in four parts
     if constexpr (P == NIV_FP16) {
-        EncodeArgs ea;
-        memset(&ea, 0, sizeof(ea));
-        ea.x = b.x;
-        ea.nrm = b.nrm;
-        ea.extra = b.extra;
-        ea.valid = b.valid;
-        ea.model = a.f[0].model;
-        ea.grid_off = a.grid_off;
-        ea.grid_bytes = a.grid_bytes;
-        ea.hash_mask = a.hash_mask;
-        ea.x_pair = reinterpret_cast<uint32_t *>(ws + L.x_off);
-        ea.x_row = reinterpret_cast<uint16_t *>(ws + L.x_off + n_chunks * S::DIN * 128);
-        ea.n = b.count;
-        for (int c = 0; c < 3; ++c) { ea.lo[c] = a.lo[c]; ea.hi[c] = a.hi[c]; }
-        hipLaunchKernelGGL(k_train_encode<S>, dim3((unsigned)(kXcds * ((n_chunks + kEncWaves - 1) / kEncWaves))),
-                           dim3(64 * kEncWaves), 0, stream, ea);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
         MlpArgs ma;
         memset(&ma, 0, sizeof(ma));
-        ma.fwd = a.f[0].model + kLevelBytes;
+        ma.fwd = sa.model + kLevelBytes;
         ma.bwd = ws + L.bwd_off;
         ma.x_pair = ea.x_pair;
-        ma.x_row = ea.x_row;
+        ma.x_row = static_cast<const uint16_t *>(ea.x_row);
         ma.x = b.x;
         ma.nrm = b.nrm;
         ma.extra = b.extra;
         ma.target = b.target;
         ma.valid = b.valid;
         ma.dw_part = dw_part;
-        ma.dx0 = dx0;
+        ma.dx0 = reinterpret_cast<float *>(ws + L.dx0_off);
         ma.sflag = ws + L.sflag_off;
         ma.status = status;
         ma.loss = st.loss;
         ma.n = b.count;
-        ma.loss_scale = a.loss_scale;
-        ma.loss_eps = a.loss_eps;
+        ma.loss_scale = sa.loss_scale;
+        ma.loss_eps = loss_eps;
         static Resident res;
-        if ((e = res.get(k_train_mlp<S>, 256, B::MLP_LDS, &bwd_blocks)) != hipSuccess) return e;
-        bwd_blocks = std::min(std::min<int64_t>(bwd_blocks, kBwdMaxBlocks), (n_chunks + 3) / 4);
-        hipLaunchKernelGGL(k_train_mlp<S>, dim3((unsigned)bwd_blocks), dim3(256), (size_t)B::MLP_LDS, stream, ma);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if ((e = res.get(k_train_mlp<S>, 256, B::MLP_LDS, &rows)) != hipSuccess) return e;
+        rows = std::min(std::min<int64_t>(rows, kBwdMaxBlocks), (n_chunks + 3) / 4);
+        hipLaunchKernelGGL(k_train_mlp<S>, dim3((unsigned)rows), dim3(256), (size_t)B::MLP_LDS, stream, ma);
     } else {
-        constexpr int kBlock = 256, kWavesPerBlock = 4;
-        auto fwd = k_query<P, S, true, 4, true, kBlock>;
-        const size_t fwd_lds = O::W_BYTES + (size_t)kWavesPerBlock * 64 * O::ROW_DW * 4;
-        static Resident fres, bres;
-        int64_t fwd_blocks = 0;
-        if ((e = fres.get(fwd, kBlock, fwd_lds, &fwd_blocks)) != hipSuccess) return e;
-        a.n_tiles = (n_chunks + kWavesPerBlock - 1) / kWavesPerBlock;
-        fwd_blocks = std::min<int64_t>(a.n_tiles, fwd_blocks);
-        hipLaunchKernelGGL(fwd, dim3((unsigned)fwd_blocks), dim3(kBlock), fwd_lds, stream, a);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        BwdArgs ba;
-        memset(&ba, 0, sizeof(ba));
-        ba.bwd = ws + L.bwd_off;
-        ba.x_save = ws + L.x_off;
-        ba.mask_save = reinterpret_cast<const uint32_t *>(ws + L.mask_off);
-        ba.dE = reinterpret_cast<const float *>(ws + L.dE_off);
-        ba.x = b.x;
-        ba.dw_part = dw_part;
-        ba.dx0 = dx0;
-        ba.sflag = ws + L.sflag_off;
-        ba.vmax = status;
-        ba.n = b.count;
-        ba.loss_scale = a.loss_scale;
-        if ((e = bres.get(k_train_bwd<S>, 256, (size_t)B::LDS_BYTES, &bwd_blocks)) != hipSuccess) return e;
-        bwd_blocks = std::min(std::min<int64_t>(bwd_blocks, kBwdMaxBlocks), (n_chunks + 3) / 4);
-        hipLaunchKernelGGL(k_train_bwd<S>, dim3((unsigned)bwd_blocks), dim3(256), (size_t)B::LDS_BYTES, stream, ba);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        using N = Net32<S>;
+        static Resident res;
+        int64_t resident = 0;
+        if ((e = res.get(k_train_net32<S>, 1024, N::LDS_BYTES, &resident)) != hipSuccess) return e;
+        rows = std::min(std::min<int64_t>(resident, kBwdMaxBlocks), (n_chunks + 3) / 4);
+        // Where the device has room, a workgroup takes one or two streams
+        // instead of four (a chunk is a chain of barriers): 64 chunks 50 ->
+        // 21 us, 313 56 -> 43, 512 62 -> 54; beyond, the workgroups would take
+        // turns (313 chunks with a workgroup each: 54 us).  The streams' rows lie where the scatter's records come
+        // later (64 KB or more per chunk: they fit).
+        const int64_t streams = 4 * rows;
+        const int wg_streams = streams <= resident ? 1 : streams <= 2 * resident ? 2 : 4;
+        quad = wg_streams < 4 && streams * B::NMLP * 4 <= b.count * S::L * 8 * 8;
+        if (quad) dw_part = reinterpret_cast<float *>(ws + L.vals_off);
+        Net32Args na;
+        memset(&na, 0, sizeof(na));
+        na.fwd = sa.model + kLevelBytes;
+        na.x_row = static_cast<const float *>(ea.x_row);
+        na.x = b.x;
+        na.nrm = b.nrm;
+        na.extra = b.extra;
+        na.target = b.target;
+        na.valid = b.valid;
+        na.dw_part = dw_part;
+        na.dx0 = reinterpret_cast<float *>(ws + L.dx0_off);
+        na.sflag = ws + L.sflag_off;
+        na.status = status;
+        na.loss = st.loss;
+        na.n = b.count;
+        na.n_streams = streams;
+        na.wg_streams = quad ? wg_streams : 4;
+        na.loss_scale = sa.loss_scale;
+        na.loss_eps = loss_eps;
+        hipLaunchKernelGGL(k_train_net32<S>, dim3((unsigned)(streams / na.wg_streams)), dim3(1024),
+                           (size_t)N::LDS_BYTES, stream, na);
     }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     // weight gradient: the workgroups' rows summed
-    hipLaunchKernelGGL(k_dw_sum, dim3((unsigned)((B::NMLP + 15) / 16)), dim3(256), 0, stream, dw_part,
-                       (int64_t)B::NMLP, (int)bwd_blocks, st.grads + m.n_grid_values, a.loss_scale);
+    hipLaunchKernelGGL(quad ? k_dw_sum<true> : k_dw_sum<false>, dim3((unsigned)((B::NMLP + 15) / 16)), dim3(256), 0, stream,
+                       dw_part, (int64_t)B::NMLP, (int)rows, st.grads + m.n_grid_values, sa.loss_scale);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // 3. grid scatter through bins (counted beside the forward, above)
     if ((e = hipStreamWaitEvent(stream, ev.join, 0)) != hipSuccess) return e;
