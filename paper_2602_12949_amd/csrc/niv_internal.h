@@ -66,6 +66,7 @@ struct QueryArgs {
     uint32_t *fb_count;       // entries appended (may exceed fb_cap)
     uint32_t fb_cap;
     int32_t xcd_order;        // tile order, see LaunchTune
+    int32_t strip_shift;      // log2 of the tiles of a strip
     FrameArgs f[kMaxFrames];
 };
 
@@ -79,10 +80,21 @@ enum ModelKind { kUnitCube = 0, kRoom = 1, kWide6D = 2, kPE16 = 3, kPE32 = 4, kP
 struct LaunchTune {
     int block;
     int blocks_per_cu;
-    int xcd_order;   // 1: the tiles go to the XCDs in strips of kStrip
+    int xcd_order;   // 1: the tiles go to the XCDs in strips, see strip_shift_of
 };
 constexpr int kXcds = 8;     // workgroups are dealt to the XCDs round robin
-constexpr int kStrip = 32;   // tiles of a strip (16,384 pixels with 512 threads)
+constexpr int kStripShift = 5;   // strips of at most 32 tiles (16,384 pixels with 512 threads)
+
+// Strips of a launch: 32 tiles, fewer where an XCD would get less than eight
+// of them and their ends would leave the XCDs uneven shares (16 tiles in
+// strips of 32 all went to one XCD: 1,024 points, room FP16, 108 us against
+// 16 us with strips of one).
+inline int strip_shift_of(int64_t n_tiles)
+{
+    int s = 0;
+    while (s < kStripShift && (n_tiles >> (s + 1)) >= 8 * kXcds) ++s;
+    return s;
+}
 
 // Operand-block layout of a prepared model (see the prepare kernel).
 struct OpLayout {

@@ -200,6 +200,7 @@ static hipError_t query_t(QueryArgs &a, const LaunchTune &tu, hipStream_t st)
         t += (chunks + waves - 1) / waves;
     }
     a.n_tiles = t;
+    a.strip_shift = strip_shift_of(t);
     if (t == 0) return hipSuccess;
     const int per_cu = (tu.blocks_per_cu > 0 && tu.blocks_per_cu < max_blocks) ? tu.blocks_per_cu : max_blocks;
     const int64_t cap = (int64_t)per_cu * n_cu;

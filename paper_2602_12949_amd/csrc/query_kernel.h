@@ -66,7 +66,7 @@ void k_query(const QueryArgs a)
     int staged = -1;  // frame whose operand block is in LDS (block-uniform)
 
     // Tile order.  Workgroup b runs on XCD b % 8; with xcd_order the tiles go
-    // to the XCDs in strips of kStrip, so that pixels close on screen, which
+    // to the XCDs in strips, so that pixels close on screen, which
     // touch the same grid cells, share an L2, and every XCD gets a like share
     // of each part of the image (a contiguous eighth of it per XCD took
     // 181-205 us where strips take 165 and the plain order 169, room
@@ -77,7 +77,9 @@ void k_query(const QueryArgs a)
     const uint32_t first = by_xcd ? blockIdx.x / kXcds : blockIdx.x;
     const uint32_t step = by_xcd ? gridDim.x / kXcds : gridDim.x;
     for (uint32_t i = first;; i += step) {
-        const uint32_t tile = by_xcd ? (i / kStrip * kXcds + blockIdx.x % kXcds) * kStrip + i % kStrip : i;
+        const uint32_t tile = by_xcd ? ((((i >> a.strip_shift) * kXcds + blockIdx.x % kXcds) << a.strip_shift) |
+                                        (i & ((1u << a.strip_shift) - 1u)))
+                                     : i;
         if (tile >= (uint64_t)a.n_tiles) break;   // fewer than 2^27 tiles (16 frames below 2^28 pixels)
         int fi = 0;
         for (int k = 1; k < a.n_frames; ++k)

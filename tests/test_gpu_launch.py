@@ -47,3 +47,16 @@ def test_wide_field_default_shapes(n):
     m.set_tune("bf16", 512, 0, 0)
     E2, _, flags2 = m.query(pos, nrm, model, "bf16", extra=extra)
     assert torch.isfinite(E).all() and torch.equal(E, E2) and torch.equal(flags, flags2)
+
+
+# few tiles: strips shorter than 32, down to one tile (tiles of one chunk at
+# these sizes: 8 and 16 tiles, then the ends of the ranges of each length)
+@pytest.mark.parametrize("tiles", [8, 16, 64, 127, 128, 255, 256])
+def test_short_strips_give_the_same_bits(tiles):
+    import torch
+    m, model, pos, nrm, extra = _setup("room_1080p", 64 * tiles - 1, "fp16")
+    E, _, flags = m.query(pos, nrm, model, "fp16", extra=extra)
+    for shape in ((512, 0, 0), (512, 0, 1), (256, 0, 1)):
+        m.set_tune("fp16", *shape)
+        E2, _, flags2 = m.query(pos, nrm, model, "fp16", extra=extra)
+        assert torch.equal(E, E2) and torch.equal(flags, flags2), shape
