@@ -266,8 +266,13 @@ LaunchTune default_tune(int kind, niv_precision prec, int64_t chunks)
     // path of a CU busy for ~8 us (points far apart), so the chunks are first
     // spread over the CUs (4,133 points, room FP16: 8 waves per workgroup
     // 57 us, one wave 22 us).
+    // The FP32 field keeps 512 threads up to three chunks: that build's waves
+    // are faster there (1, 2, 3 chunks 81, 81, 85 us against 93 us with 64
+    // threads; 4 chunks 102 against 94, 8 chunks 221 against 94).
     if (kind == kWide6D && prec != NIV_FP32) {
         if (chunks <= 4 * kCus) t.block = 256;
+    } else if (kind == kWide6D && chunks <= 3) {
+        t.block = 512;
     } else if (chunks <= kCus) {
         t.block = 64;
     } else if (chunks <= 2 * kCus) {

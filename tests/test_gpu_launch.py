@@ -60,3 +60,14 @@ def test_short_strips_give_the_same_bits(tiles):
         m.set_tune("fp16", *shape)
         E2, _, flags2 = m.query(pos, nrm, model, "fp16", extra=extra)
         assert torch.equal(E, E2) and torch.equal(flags, flags2), shape
+
+
+@pytest.mark.parametrize("n", [64 * 3, 64 * 3 + 1])
+def test_wide_field_fp32_small_shapes(n):
+    import torch
+    m, model, pos, nrm, extra = _setup("room_4k_6d", n, "fp32")
+    E, _, flags = m.query(pos, nrm, model, "fp32", extra=extra)
+    for shape in ((512, 0, 0), (256, 0, 0)):
+        m.set_tune("fp32", *shape)
+        E2, _, flags2 = m.query(pos, nrm, model, "fp32", extra=extra)
+        assert torch.isfinite(E).all() and torch.equal(E, E2) and torch.equal(flags, flags2), shape
